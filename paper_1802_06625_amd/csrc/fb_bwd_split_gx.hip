@@ -469,8 +469,11 @@ __global__ __launch_bounds__(64 * kGxWaves, 2) void k_bwd_gx_split(prune_fb_desc
   const int H = (int)Lmax - 1;
   const uint32_t ni = *n_items, total = ni + (H > 0 ? d.n_frames : 0u), ng = (total + kGxGroup - 1) / kGxGroup;
   const uint32_t kfull = (1u << d.Kmax) - 1u;
+  // what the tap table holds: a bank's powers (tab_bank), or the sums of a
+  // mask over several banks (tab_bank -1; every bit of the mask may be a branch)
   const float2 *tab_taps = nullptr;
-  uint32_t tab_key = 0, par = 0;
+  int tab_bank = -1;
+  uint32_t tab_mask = 0, par = 0;
   const bool tickets = 2ull * gridDim.x < ng;
   // a group's entries, read a group ahead
   auto entries = [&](uint32_t grp, uint32_t buf) {
@@ -512,10 +515,11 @@ __global__ __launch_bounds__(64 * kGxWaves, 2) void k_bwd_gx_split(prune_fb_desc
         if (my) copy_out(F.route ? F.g : nullptr, o, lane);
         continue;
       }
-      const uint32_t key = bank1 >= 0 ? 0x80000000u | (uint32_t)bank1 : F.mask;
-      if (F.taps != tab_taps || key != tab_key) {   // uniform across the workgroup
+      const uint32_t tm = bank1 >= 0 ? 0u : F.mask;
+      if (F.taps != tab_taps || bank1 != tab_bank || tm != tab_mask) {   // uniform across the workgroup
         tab_taps = F.taps;
-        tab_key = key;
+        tab_bank = bank1;
+        tab_mask = tm;
         __syncthreads();
         gx_table(d, F, Lmax, bank1, L <= 33 ? 6 : L <= 49 ? 8 : 10, sh);
       }

@@ -454,8 +454,11 @@ __global__ __launch_bounds__(256, 2) void k_fb_split(const FbFrameDesc *__restri
   uint32_t *plane = s_plane[w][0];
   const uint32_t n_items = *n_items_ptr;
   const bool tickets = 2ull * gridDim.x < n_items;
+  // what the tap table holds: a bank's powers (tab_bank), or the sums of a
+  // mask over several banks (tab_bank -1; every bit of the mask may be a branch)
   const float2 *tab_taps = nullptr;
-  uint32_t tab_key = 0, par = 0;
+  int tab_bank = -1;
+  uint32_t tab_mask = 0, par = 0;
   pair_u v[NPM];
   auto pass_nt = [&](int left) { return NTMAX > 1 && left > 2048 ? 2 : 1; };
   CItem *const list = (CItem *)items;
@@ -492,10 +495,11 @@ __global__ __launch_bounds__(256, 2) void k_fb_split(const FbFrameDesc *__restri
       }
       prefetch_window<NTMAX>(next_item, lane, v);
     } else {
-      const uint32_t key = bank1 >= 0 ? 0x80000000u | (uint32_t)bank1 : d.mask;
-      if (d.taps != tab_taps || key != tab_key) {   // uniform across the workgroup
+      const uint32_t tm = bank1 >= 0 ? 0u : d.mask;
+      if (d.taps != tab_taps || bank1 != tab_bank || tm != tab_mask) {   // uniform across the workgroup
         tab_taps = d.taps;
-        tab_key = key;
+        tab_bank = bank1;
+        tab_mask = tm;
         if (L <= 33) build_table<6>(d, bank1, sh);
         else if (L <= 49) build_table<8>(d, bank1, sh);
         else build_table<10>(d, bank1, sh);
