@@ -1,0 +1,127 @@
+"""Split half-precision kernels where an output depends on operands far below
+the largest of its wave's window: quiet stretches beside loud ones with the
+high powers in front, masks and taps without the first power, taps that leave
+the loud samples out, single samples in silence, stream starts and frame ends.
+
+Forward, per output: |y - ref| <= 2^-17 sum |h| |u|, the kernels' own bound
+(110 roundings of 2^-24), and 1e-44 for fp32's underflow."""
+import numpy as np
+import pytest
+import torch
+
+from oracle.filterbank import fb_stream
+from paper_1802_06625_amd import ops
+
+from gpu_util import announce
+
+pytestmark = pytest.mark.gpu
+BOUND = 2.0 ** -17
+
+
+@pytest.fixture(autouse=True)
+def _needs_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _c(rng, *shape):
+    return (rng.standard_normal(shape) + 1j * rng.standard_normal(shape)).astype(np.complex64)
+
+
+def _forward(variant, x, taps, rows, K, L, what):
+    ops.set_variant(variant)
+    try:
+        y = ops.fb_forward(torch.from_numpy(x[None]).cuda(), torch.from_numpy(taps[None, None]).cuda(),
+                           ops.frame_table([(0, *r, 0) for r in rows]), K, (L,), max(r[1] for r in rows))
+        y = y[0].cpu().numpy().astype(np.complex128)
+    finally:
+        ops.set_variant(0)
+    fr = [(*r, 0) for r in rows]
+    ref = fb_stream(x, fr, taps[None], (L,), K)
+    size = fb_stream(np.abs(x.astype(complex)), fr, np.abs(taps[None].astype(complex)), (L,), K).real
+    off = np.abs(y - ref)
+    worst = int(np.argmax(off / np.maximum(size, 1e-40)))
+    assert np.all(off <= BOUND * size + 1e-44), (what, worst, off[worst] / max(size[worst], 1e-40))
+    return y
+
+
+@pytest.mark.parametrize("variant", [6, 8])
+@pytest.mark.parametrize("L", [25, 64])
+@pytest.mark.parametrize("sigma,step,K,zero", [(30, 5, 10, 0), (4, 4, 10, 0), (8, 5, 6, 0), (0.3, 9, 3, 1), (0.3, 9, 3, 2),
+                                               (0.3, 12, 1, 0), (0.3, 25, 2, 0), (1, 1, 10, 9)])
+def test_quiet_stretches(sigma, step, K, zero, L, variant):
+    """Stretches of 300 samples at 2^-step of the rest; the taps of the first
+    `zero` powers are zero though their branches are in the mask."""
+    announce(f"quiet stretches sigma {sigma} step {step} K {K} zero {zero} L {L} variant {variant}")
+    rng = np.random.default_rng(K + 100 * L)
+    x = _c(rng, 5000) * np.float32(sigma)
+    for a in (700, 2000, 3333):
+        x[a:a + 300] *= np.float32(2.0 ** -step)
+    taps = _c(rng, K, L)
+    taps[:zero] = 0
+    _forward(variant, x, taps, [(0, 5000, (1 << K) - 1)], K, L, "stretch")
+
+
+@pytest.mark.parametrize("K", [5, 10])
+@pytest.mark.parametrize("P", [4, 8, 16, 64])
+def test_quiet_frame_after_a_loud_one(P, K):
+    announce(f"quiet after loud, {P}:1, K {K}")
+    rng = np.random.default_rng(P)
+    x = np.exp(2j * np.pi * rng.uniform(size=1700)).astype(np.complex64)
+    x[:64] *= P
+    x[1000:1064] *= P
+    _forward(6, x, _c(rng, K, 32), [(0, 1064, (1 << K) - 1), (1064, 300, (1 << K) - 1), (1364, 336, (1 << K) - 1)], K, 32,
+             "frame")
+
+
+@pytest.mark.parametrize("mask", [0x2, 0x200, 0x3FE, 0x2AA, 0x60])
+def test_masks_without_the_first_power(mask):
+    announce(f"mask {mask:#x}")
+    rng = np.random.default_rng(mask)
+    for sigma in (0.3, 1.0, 50.0):
+        x = _c(rng, 4000) * np.float32(sigma)
+        x[1500:1600] *= np.float32(0.05)
+        _forward(7, x, _c(rng, 10, 30), [(0, 4000, mask)], 10, 30, sigma)
+
+
+@pytest.mark.parametrize("share", [0.2, 0.002])   # whole waves, and outputs one by one
+@pytest.mark.parametrize("taps_of", ["one", "first", "decaying", "two scales"])
+def test_taps_that_leave_samples_out(taps_of, share):
+    announce(f"taps {taps_of}, share {share}")
+    rng = np.random.default_rng(7)
+    K, L = 3, 40
+    x = _c(rng, 4000)
+    x[rng.uniform(size=4000) < share] *= np.float32(1e-9)
+    taps = _c(rng, K, L)
+    if taps_of == "one":
+        taps[:, np.arange(L) != 11] = 0
+    elif taps_of == "first":
+        taps[:, 1:] = 0
+    elif taps_of == "decaying":
+        taps *= np.exp2(-2.0 * np.arange(L)).astype(np.float32)
+    else:
+        taps[:, ::2] *= np.float32(1e-11)
+    _forward(6, x, taps, [(0, 4000, 7)], K, L, taps_of)
+
+
+@pytest.mark.parametrize("variant", [6, 7, 8])
+def test_beside_silence(variant):
+    """A stream that begins with a tiny sample, tails before silence, single
+    samples in it; outputs of silent windows are exact zeros."""
+    announce(f"beside silence, variant {variant}")
+    rng = np.random.default_rng(variant)
+    K, L, n = 4, 25, 6000
+    x = _c(rng, n) * np.float32(0.3)
+    x[0] = 1e-9
+    x[1000:1003] *= np.float32(1e-10)
+    x[1003:1200] = 0
+    x[2000:2300] = 0
+    x[2100] = 1e-12 + 1e-13j
+    x[3000:5100] = 0
+    x[5100] *= np.float32(1e-11)
+    x[n - 1] *= np.float32(1e-10)
+    taps = _c(rng, K, L)
+    y = _forward(variant, x, taps, [(0, 2050, 15), (2050, 1500, 15), (3550, n - 3550, 15)], K, L, "silence")
+    for a, b in ((1003, 1200), (2000, 2100), (2101, 2300), (3000, 5100)):
+        assert np.all(y[a + L - 1:b] == 0)
+    assert np.all(_forward(variant, x, taps * 0, [(0, n, 15)], K, L, "no taps") == 0)
