@@ -11,19 +11,23 @@
 // runs forward in time and the Hankel matrix is g's.  g does not depend on the
 // power: its two half-precision parts are written to the wave's LDS planes
 // once and serve every power; P is a Horner sum over the powers, from the
-// highest down, in fp32 registers, and Q = (r/2) dP/dr its derivative's.  Taps of several banks are added first (the
-// sum over banks of one power).
+// highest down, in fp32 registers, and Q = (r/2) dP/dr its derivative's.  Taps
+// of several banks are added first (the sum over banks of one power).
 //
-// Precision.  As in the forward: g scaled by a power of two per wave, the taps
-// per power, high x high + low x high + high x low summed per power with the
-// low products first.  A wave falls back to products of fp32 on the matrix
-// core where a run of eight samples of g is not zero and more than 2^11 below
-// the window's largest, where g or taps are not finite or beyond 2^93, or
-// where |x| reaches 2^8 or is not zero and below 2^-59.  (Below 15 taps an
-// output's window need not hold a whole run.)  Relative error against fp64 for
-// 15 to 64 taps: 0.9e-7 to 1.3e-7 for one power, 2.2e-7 to 2.5e-7 for eight of
-// constant envelope, where products of fp32 have 1.0e-7 to 2.3e-7 and 2.4e-7
-// to 2.9e-7.
+// Precision.  As in the forward: g scaled by a power of two per wave (and r, so
+// that its powers stay below one), the taps per power, high x high + low x high
+// + high x low summed per power with the low products first.  Relative error
+// against fp64 for 15 to 64 taps: 0.9e-7 to 1.3e-7 for one power, 2.2e-7 to
+// 2.5e-7 for eight of constant envelope, where products of fp32 have 1.0e-7 to
+// 2.3e-7 and 2.4e-7 to 2.9e-7.  What g's parts can miss of it (2^-25 of the
+// scaled g a tap, as in the forward) is compared with the outputs: with HS_p
+// the sum of the magnitudes of power p's scaled taps and T = 2^-25 sum_p
+// 1.5 (1 + p) HS_p r^p, a wave takes products of fp32 on the matrix core
+// instead where an output's |P| is below 2^17 T, or all of a lane's are below
+// 2^20 T.  Outputs before which g is zero over the filter's length are exact
+// zeros and stay.  So does a wave whose g or taps are not finite or beyond
+// 2^93, or whose |x| reaches 2^59 or is not zero and below 2^-59.  Gaussian
+// samples have their |P|'s median near 2^33 T.
 //
 // What bounds it.  1024 frames x 32768 of 64 streams, 30 % of them skipped, 64
 // taps, 7 powers: 430 us, from 790 us for products of fp32 on the matrix core
@@ -45,13 +49,16 @@ constexpr int kGxWaves = 4;
 constexpr int kGxPow = 10;                       // powers of a bank
 constexpr int kGxTab = PRUNE_MAX_L + 32;         // table entries per power: 8 S + 16 at most
 constexpr int kGxGroup = kGxWaves;               // list entries per ticket
-constexpr int kTapBits = 15, kCotBits = 11;      // largest tap scaled below 2^15, cotangent below 2^11
+constexpr int kTapBits = 15, kCotBits = 15;      // largest tap and cotangent component scaled below 2^15
+constexpr float kGxMargin = 0x1p-8f;             // 2^17 times an operand's 2^-25
+constexpr float kHuge = 3e38f;
 constexpr int kNoTap = -100000, kBadTap = 100000;
-constexpr uint32_t kTinyX = 8u << 23, kLargeX = (127u + 16u) << 23;   // |x|^2 from 2^-119 to 2^16 (or zero)
+constexpr uint32_t kTinyX = 8u << 23, kLargeX = (127u + 119u) << 23;   // |x|^2 from 2^-119 to 2^119 (or zero)
 
 struct GxShared {
   uint32_t tab[kGxPow][2][2][kGxTab];            // [power][high, low part][re, im row][tap + 15]
   int cexp[16];                                  // per power: its largest tap is below 2^cexp
+  int hsum[16];                                  // per power: HS_p, and 2^16 for each component below one half
   BwdFrame frame[2][kGxGroup];                   // the entries of this group and of the next
   int n0[2][kGxGroup];
   uint32_t at[2][kGxGroup];                      // frame index
@@ -73,7 +80,10 @@ __device__ __forceinline__ void gx_table(const prune_fb_desc &d, const BwdFrame 
   const int TS = 8 * S + 16;
   int t = threadIdx.x;
   asm volatile("" : "+v"(t));
-  if (t < 16) sh.cexp[t] = kNoTap;
+  if (t < 16) {
+    sh.cexp[t] = kNoTap;
+    sh.hsum[t] = 0;
+  }
   __syncthreads();
   float2 h[4];
 #pragma unroll
@@ -100,7 +110,10 @@ __device__ __forceinline__ void gx_table(const prune_fb_desc &d, const BwdFrame 
     const int k = t + 64 * kGxWaves * i, p = k / TS, q = k - p * TS;
     if (p < kGxPow) {
       const int sc = kTapBits - sh.cexp[p];
-      const float hr = ldexpf(h[i].x, sc), hi = ldexpf(h[i].y, sc);
+      const float hr = ldexpf(h[i].x, sc), hi = ldexpf(h[i].y, sc), ar = fabsf(hr), ai = fabsf(hi);
+      if (ar + ai > 0.f && sh.cexp[p] != kBadTap)
+        atomicAdd(&sh.hsum[p], (int)ceilf(ar + ai) + (ar > 0.f && ar < 0.5f ? 1 << 16 : 0) +
+                                   (ai > 0.f && ai < 0.5f ? 1 << 16 : 0));
       const _Float16 r1 = (_Float16)hr, i1 = (_Float16)hi;
       const _Float16 r2 = (_Float16)(hr - (float)r1), i2 = (_Float16)(hi - (float)i1);
       sh.tab[p][0][0][q] = __builtin_bit_cast(uint32_t, half2v{r1, i1});
@@ -171,6 +184,8 @@ __device__ __forceinline__ void copy_out(const float2 *g, GxOut o, int lane) {
 
 // A wave's gradients at positions wb .. wb + 512 nt - 1 from products of fp32
 // (16 x 16 blocks, steps of four positions, three real products a complex one).
+// A branch's taps, zeros on either side, follow g in the planes.
+constexpr int kGxTapAt = 512 * 2 + 80, kGxTapLen = PRUNE_MAX_L + 32;
 __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, uint32_t Lmax, int wb, int nt, GxOut o,
                                      float *plane, int pitch, int lane) {
   const int n = (int)F.n, li = lane & 15, lk = lane >> 4;
@@ -202,10 +217,17 @@ __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, 
         if (!((F.mask >> (bank * d.Kmax)) & kfull & (1u << p))) continue;
         const int L = (int)d.L[bank];
         const float2 *tb = F.taps + (size_t)(bank * d.Kmax + p) * Lmax;
+        wave_lds_fence();
+        for (int k = lane; k < kGxTapLen; k += 64) {
+          const float2 h = k >= 16 && k - 16 < L ? ld_global(tb + (k - 16)) : make_float2(0.f, 0.f);
+          plane[kGxTapAt + k] = h.x;
+          plane[pitch + kGxTapAt + k] = h.y;
+        }
+        wave_lds_fence();
         floatx4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0, a2 = a0;
         for (int s = 0; s < (L + 15 + 3) / 4; ++s) {
-          const int l = 4 * s + lk - li;
-          const float2 h = l >= 0 && l < L ? ld_global(tb + l) : make_float2(0.f, 0.f);
+          const int l = kGxTapAt + 16 + 4 * s + lk - li;
+          const float2 h = make_float2(plane[l], plane[pitch + l]);
           const int w = 256 * t + 16 * li + 4 * s + lk;
           const float gr = plane[w], gi = plane[pitch + w];
           a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.x, gr, a0, 0, 0, 0);
@@ -232,11 +254,52 @@ __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, 
   wave_lds_fence();
 }
 
+// A lane's output b of a wave (in the order of gx_pass): its place from wb.
+template <int NT>
+__device__ __forceinline__ int output_at(int lane, int b) {
+  return 16 * NT * (lane & 31) + 2 * (lane >> 5) + 16 * (b >> 3) + 4 * ((b >> 1) & 3) + (b & 1);
+}
+
+// Whether g is zero over the L samples from each output in `zeros` (a bit for
+// each of the lane's) on.
+template <int NT>
+__device__ __noinline__ bool silent_after(const BwdFrame &F, int wb, int L, uint32_t zeros, uint32_t *plane, int lane) {
+  const int n = (int)F.n;
+  const unsigned long long ge = ~0ull << lane, gt = lane < 63 ? ~0ull << (lane + 1) : 0ull;
+  auto low = [](unsigned long long m) { return m ? __ffsll(m) - 1 : 1 << 20; };
+  int next = 1 << 20;                          // the first sample after this run that is not zero
+  wave_lds_fence();
+  for (int i = 4 * NT; i >= 0; --i) {
+    unsigned long long on[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int p = wb + 2 * lane + 128 * i + q;
+      const float2 z = p >= 0 && p < n ? ld_global(F.g + p) : make_float2(0.f, 0.f);
+      on[q] = __ballot((abs_bits(z.x) | abs_bits(z.y)) != 0u);
+    }
+    const int k = 128 * i, odd = 2 * low(on[1] & ge) + 1;
+    plane[k + 2 * lane] = (uint32_t)min(next, k + min(odd, 2 * low(on[0] & ge)));
+    plane[k + 2 * lane + 1] = (uint32_t)min(next, k + min(odd, 2 * low(on[0] & gt)));
+    next = min(next, k + min(2 * low(on[0]), 2 * low(on[1]) + 1));
+  }
+  wave_lds_fence();
+  bool ok = true;
+  for (int b = 0; b < 8 * NT; ++b) {
+    const int k = output_at<NT>(lane, b);
+    if ((zeros >> b) & 1u) ok &= (int)plane[k] - k >= L;
+  }
+  wave_lds_fence();
+  return !__any(!ok);
+}
+
 // One pass of one wave: positions wb .. wb + 512 NT - 1 (32 columns of 16 NT).
-// Returns true, with nothing written, where it is left to gx_fp32.
+// kPassLeft: nothing is written, the outputs are left to gx_fp32.  kPassZeros:
+// everything is written, and right if g is zero after the outputs in `zeros`
+// (silent_after); else the outputs are left to gx_fp32.
+enum { kPassDone, kPassLeft, kPassZeros };
 template <int NT, int S, int PLANE>
-__device__ __forceinline__ bool gx_pass(const BwdFrame &F, int wb, uint32_t pm, GxOut o, const GxShared &sh,
-                                        uint32_t *__restrict__ plane, int lane) {
+__device__ __forceinline__ int gx_pass(const BwdFrame &F, int wb, uint32_t pm, GxOut o, const GxShared &sh,
+                                       uint32_t *__restrict__ plane, int lane, uint32_t &zeros) {
   constexpr int NP = 4 * NT + 1;               // sample pairs per lane
   constexpr int NC = 2 * NT + S - 2;           // chunk pairs per column
   constexpr int CW = 4 * NT;                   // chunks per column
@@ -304,28 +367,26 @@ __device__ __forceinline__ bool gx_pass(const BwdFrame &F, int wb, uint32_t pm, 
         rr[j][2 * q + 1] = z.y;
       }
   }
-  uint32_t cb[NP], am = 0;
+  const uint32_t S2 = (uint32_t)wave_max((int)min(s_max, kInf));   // the largest |x|^2, or not finite
+  const int ex = S2 ? ((int)(S2 >> 23) - 125) >> 1 : 0;            // |x| < 2^ex
+  const float rs = ldexpf(1.f, -ex);
 #pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    cb[i] = max(max(abs_bits(v[i].x), abs_bits(v[i].y)), max(abs_bits(v[i].z), abs_bits(v[i].w)));
-    am = max(am, cb[i]);
-  }
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) rr[j][q] *= rs;
+  uint32_t am = 0;
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+    am = max(max(am, max(abs_bits(v[i].x), abs_bits(v[i].y))), max(abs_bits(v[i].z), abs_bits(v[i].w)));
   const uint32_t A = (uint32_t)wave_max((int)am);
   const int e = A >= kLow ? (int)(A >> 23) - 126 : 0;   // |re|, |im| < 2^e
   int ep = kNoTap;
   if (lane < kGxPow && ((pm >> lane) & 1u)) ep = sh.cexp[lane];
-  bool bad = __any(ep == kBadTap) || (A != 0 && (A < kLow || A >= kHigh)) ||
-             __any(s_min < kTinyX || s_max >= kLargeX);
+  if (__any(ep == kBadTap) || (A != 0 && (A < kLow || A >= kHigh)) || S2 >= kLargeX || __any(s_min < kTinyX))
+    return kPassLeft;
+  ep += lane * ex;
   const int eb = wave_max(ep);
   const float ef = ldexpf(1.f, max(ep - eb, -200));
-  const uint32_t thr = A >= kLow ? A - ((uint32_t)kCotBits << 23) : 0u;
-  bool quiet = false;
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const uint32_t m = __builtin_bit_cast(uint32_t, quad_max(__builtin_bit_cast(float, cb[i])));
-    quiet |= m < thr && m > 0u;
-  }
-  if (bad || __any(quiet)) return true;
   float neg1 = -1.f;
   asm volatile("" : "+v"(neg1));
   const float gs = __builtin_bit_cast(float, (uint32_t)(127 + kCotBits - e) << 23);
@@ -411,6 +472,52 @@ __device__ __forceinline__ bool gx_pass(const BwdFrame &F, int wb, uint32_t pm, 
     if (next < 0) break;
     p = next;
   }
+  // the outputs against what may be missing of them: against T at the largest
+  // r first, and each against its own where that does not settle it (at least
+  // 2^-80, so that no power that is missing for its ef or by underflow counts)
+  zeros = 0;
+  if (A != 0 && eb > kNoTap / 2) {
+    auto size = [&](int b) {
+      const int j = b >> 3, q = 2 * (b & 7), m = wb + output_at<NT>(lane, b);
+      return m >= o.lo && m < o.hi ? fmaxf(fabsf(P[j][q]), fabsf(P[j][q + 1])) : kHuge;
+    };
+    const float tv = (pm >> (lane & 15)) & 1u ? kGxMargin * 1.5f * (1 + (lane & 15)) * ef * (float)sh.hsum[lane & 15] : 0.f;
+    auto term = [&](int p) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, tv), p));
+    };
+    const int top = 31 - __clz(pm);
+    const float rm = rs * __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, S2));
+    float tm = 0x1p-80f, least = kHuge;
+    for (int p = top; p >= 0; --p) tm = fmaf(tm, rm, term(p));
+    const bool whole = wb >= o.lo && wb + 512 * NT <= o.hi;   // uniform
+#pragma unroll
+    for (int b = 0; b < 8 * NT; ++b)
+      least = fminf(least, whole ? fmaxf(fabsf(P[b >> 3][2 * (b & 7)]), fabsf(P[b >> 3][2 * (b & 7) + 1])) : size(b));
+    if (__any(least < 8.f * fmaxf(tm, 0x1p-80f))) {
+      bool low = false, quiet = true, some = false;
+      for (int j = 0; j < NT; ++j) {
+        float T[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) T[b] = 0.f;
+        for (int p = top; p >= 0; --p) {
+          const float t = term(p);
+#pragma unroll
+          for (int b = 0; b < 8; ++b) T[b] = fmaf(T[b], NT > 1 && j ? rr[NT - 1][b] : rr[0][b], t);
+        }
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          const float r = NT > 1 && j ? rr[NT - 1][b] : rr[0][b];
+          const float m = NT > 1 && j ? size(8 * (NT - 1) + b) : size(b);
+          const float thr = r > 0.f || (pm & 1u) ? fmaxf(T[b], 0x1p-80f) : 0.f;
+          low |= m > 0.f && m < thr;
+          quiet &= m < 8.f * thr || m == kHuge;
+          some |= m > 0.f && m < kHuge;
+          zeros |= m == 0.f && thr > 0.f ? 1u << (8 * j + b) : 0u;
+        }
+      }
+      if (__any(low || (quiet && some))) return kPassLeft;
+    }
+  }
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -442,7 +549,7 @@ __device__ __forceinline__ bool gx_pass(const BwdFrame &F, int wb, uint32_t pm, 
       else if (m + 1 >= o.lo && m + 1 < o.hi) st_global(o.gx + m + 1, make_float2(z.z, z.w));
     }
   }
-  return false;
+  return __any(zeros != 0u) ? kPassZeros : kPassDone;
 }
 }  // namespace
 
@@ -459,6 +566,7 @@ __global__ __launch_bounds__(64 * kGxWaves, 2) void k_bwd_gx_split(prune_fb_desc
                                                                    const uint32_t *__restrict__ sfirst,
                                                                    float2 *__restrict__ gxs) {
   constexpr int PL = gx_plane(2);
+  static_assert(PL >= kGxTapAt + kGxTapLen, "g and a branch's taps fit in a plane");
   static_assert(2 * PL >= 2 * 4 * 288 && gx_plane(1) <= PL, "P and Q of a tile, and one-tile passes, fit in the planes");
   __shared__ GxShared sh;
   __shared__ __align__(16) uint32_t s_plane[kGxWaves][2][PL];
@@ -525,17 +633,25 @@ __global__ __launch_bounds__(64 * kGxWaves, 2) void k_bwd_gx_split(prune_fb_desc
       }
       if (!my) continue;
       const int nt = !halo && n - n0 > 512 ? 2 : 1;
-      bool left_out;
+      int end;
+      uint32_t zeros = 0;
       if (nt == 2) {
-        if (L <= 33) left_out = gx_pass<2, 6, PL>(F, n0, pm, o, sh, plane, lane);
-        else if (L <= 49) left_out = gx_pass<2, 8, PL>(F, n0, pm, o, sh, plane, lane);
-        else left_out = gx_pass<2, 10, PL>(F, n0, pm, o, sh, plane, lane);
+        if (L <= 33) end = gx_pass<2, 6, PL>(F, n0, pm, o, sh, plane, lane, zeros);
+        else if (L <= 49) end = gx_pass<2, 8, PL>(F, n0, pm, o, sh, plane, lane, zeros);
+        else end = gx_pass<2, 10, PL>(F, n0, pm, o, sh, plane, lane, zeros);
       } else {
-        if (L <= 33) left_out = gx_pass<1, 6, PL>(F, n0, pm, o, sh, plane, lane);
-        else if (L <= 49) left_out = gx_pass<1, 8, PL>(F, n0, pm, o, sh, plane, lane);
-        else left_out = gx_pass<1, 10, PL>(F, n0, pm, o, sh, plane, lane);
+        if (L <= 33) end = gx_pass<1, 6, PL>(F, n0, pm, o, sh, plane, lane, zeros);
+        else if (L <= 49) end = gx_pass<1, 8, PL>(F, n0, pm, o, sh, plane, lane, zeros);
+        else end = gx_pass<1, 10, PL>(F, n0, pm, o, sh, plane, lane, zeros);
       }
-      if (left_out) gx_fp32(d, sh.frame[par][k], Lmax, n0, nt, o, (float *)plane, PL, lane);
+      if (end == kPassZeros) {
+        const bool silent = nt == 2 ? silent_after<2>(sh.frame[par][k], n0, L, zeros, plane, lane)
+                                    : silent_after<1>(sh.frame[par][k], n0, L, zeros, plane, lane);
+        if (!silent) end = kPassLeft;
+        __builtin_amdgcn_s_waitcnt(0);         // for the outputs that are written again
+        asm volatile("" ::: "memory");
+      }
+      if (end == kPassLeft) gx_fp32(d, sh.frame[par][k], Lmax, n0, nt, o, (float *)plane, PL, lane);
     }
     __syncthreads();
     grp = grp1;

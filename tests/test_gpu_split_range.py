@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle.filterbank import fb_stream
+from oracle.filterbank import fb_stream, fb_stream_adjoint
 from paper_1802_06625_amd import ops
 
 from gpu_util import announce
@@ -125,3 +125,85 @@ def test_beside_silence(variant):
     for a, b in ((1003, 1200), (2000, 2100), (2101, 2300), (3000, 5100)):
         assert np.all(y[a + L - 1:b] == 0)
     assert np.all(_forward(variant, x, taps * 0, [(0, n, 15)], K, L, "no taps") == 0)
+
+
+# ---- grad_x: per sample |grad - ref| <= 2^-16 sum_p (1 + p) r^p sum_l |h| |g|
+# (2^-17 that may be missing of g's parts, and the roundings as above)
+def _grad_x(x, g, taps, rows, K, L, what):
+    ops.set_bwd_variant(2)
+    try:
+        gx, _ = ops.fb_backward(torch.from_numpy(x[None]).cuda(), torch.from_numpy(taps[None, None]).cuda(),
+                                ops.frame_table([(0, *r, 0) for r in rows]), torch.from_numpy(g[None]).cuda(), K, (L,),
+                                max(r[1] for r in rows))
+        gx = gx[0].cpu().numpy().astype(np.complex128)
+    finally:
+        ops.set_bwd_variant(0)
+    ref, _ = fb_stream_adjoint(x, [(*r, 0) for r in rows], taps[None], (L,), K, g)
+    size, r = np.zeros(len(x)), np.abs(x.astype(complex))
+    for (t0, n, m) in rows:
+        for p in range(K):
+            if (m >> p) & 1:
+                G = np.convolve(np.abs(g[t0:t0 + n].astype(complex)), np.abs(taps[p].astype(complex))[::-1])
+                lo = max(0, t0 - L + 1)
+                G = G[lo - (t0 - L + 1):]
+                size[lo:lo + len(G)] += G * (1 + p) * r[lo:lo + len(G)] ** p
+    off = np.abs(gx - ref)
+    worst = int(np.argmax(off / np.maximum(size, 1e-40)))
+    assert np.all(off <= 2.0 ** -16 * size + 1e-44), (what, worst, off[worst] / max(size[worst], 1e-40))
+    return gx
+
+
+@pytest.mark.parametrize("L", [15, 40, 64])
+@pytest.mark.parametrize("step", [8, 13, 17, 30])
+def test_grad_x_quiet_cotangent(step, L):
+    announce(f"grad_x, cotangent at 2^-{step}, L {L}")
+    rng = np.random.default_rng(step + L)
+    x, g, K = _c(rng, 5000) * np.float32(0.3), _c(rng, 5000), 6
+    for a in (700, 2000, 3333):
+        g[a:a + 300] *= np.float32(2.0 ** -step)
+    _grad_x(x, g, _c(rng, K, L), [(0, 2800, 63), (2800, 2200, 62)], K, L, "cotangent")
+
+
+@pytest.mark.parametrize("K", [1, 4])
+def test_grad_x_beside_zeros(K):
+    """Tiny last samples of a frame, single and tiny cotangents among zeros;
+    gradients before zeros alone are exact zeros."""
+    announce(f"grad_x beside zeros, K {K}")
+    rng = np.random.default_rng(K)
+    n, L = 6000, 25
+    x, g = _c(rng, n) * np.float32(0.3), _c(rng, n)
+    g[1500] *= np.float32(1e-10)
+    g[1497:1500] = 0
+    g[1999] *= np.float32(1e-12)
+    g[3000:3300] = 0
+    g[3100] = 1e-11
+    g[4000:5500] = 0
+    g[5500:5503] *= np.float32(1e-9)
+    x[2500:2600] = 0
+    gx = _grad_x(x, g, _c(rng, K, L), [(0, 2000, (1 << K) - 1), (2000, 1001, (1 << K) - 1),
+                                      (3001, 2999, (1 << K) - 1)], K, L, "zeros")
+    assert np.all(gx[4000:5500 - L] == 0) and np.all(gx[3101:3300 - L] == 0)
+
+
+@pytest.mark.parametrize("mask", [0x3FF, 0x200, 0x2A4])
+@pytest.mark.parametrize("what", ["units of 3000", "loud and quiet", "tiny", "one tap", "decaying taps"])
+def test_grad_x_samples_and_taps(what, mask):
+    announce(f"grad_x {what}, mask {mask:#x}")
+    rng = np.random.default_rng(mask)
+    K, L, n = 10, 30, 4000
+    x, g, taps = _c(rng, n) * np.float32(0.3), _c(rng, n), _c(rng, K, L)
+    if what == "units of 3000":
+        x *= np.float32(1e4)
+        taps[4:] *= np.float32(1e-20)
+    elif what == "loud and quiet":
+        x[500:900] *= 30
+        x[1500:1600] *= np.float32(0.01)
+    elif what == "tiny":
+        x *= np.float32(1e-3)
+    elif what == "one tap":
+        taps[:, np.arange(L) != 11] = 0
+        g[rng.uniform(size=n) < 0.1] *= np.float32(1e-9)
+    else:
+        taps *= np.exp2(-2.0 * np.arange(L)).astype(np.float32)
+        g[rng.uniform(size=n) < 0.1] *= np.float32(1e-9)
+    _grad_x(x, g, taps, [(0, n, mask)], K, L, what)
