@@ -22,12 +22,13 @@
 // 2.3e-7 and 2.4e-7 to 2.9e-7.  What g's parts can miss of it (2^-25 of the
 // scaled g a tap, as in the forward) is compared with the outputs: with HS_p
 // the sum of the magnitudes of power p's scaled taps and T = 2^-25 sum_p
-// 1.5 (1 + p) HS_p r^p, a wave takes products of fp32 on the matrix core
-// instead where an output's |P| is below 2^17 T, or all of a lane's are below
-// 2^20 T.  Outputs before which g is zero over the filter's length are exact
-// zeros and stay.  So does a wave whose g or taps are not finite or beyond
-// 2^93, or whose |x| reaches 2^59 or is not zero and below 2^-59.  Gaussian
-// samples have their |P|'s median near 2^33 T.
+// 1.5 (1 + p) HS_p r^p, outputs whose |P| is below 2^17 T are evaluated one by
+// one in fp32 instead; a wave that has more than kFew of them, or a lane with
+// all of its outputs (sixteen of 32 in a row) below 2^20 T, takes products of
+// fp32 on the matrix core, and so does a wave whose g or taps are not finite or
+// beyond 2^93, or whose |x| reaches 2^59 or is not zero and below 2^-59.
+// Outputs from which on g is zero over the filter's length are exact zeros and
+// stay.  Gaussian samples have their |P|'s median near 2^33 T.
 //
 // What bounds it.  1024 frames x 32768 of 64 streams, 30 % of them skipped, 64
 // taps, 7 powers: 430 us, from 790 us for products of fp32 on the matrix core
@@ -184,8 +185,9 @@ __device__ __forceinline__ void copy_out(const float2 *g, GxOut o, int lane) {
 
 // A wave's gradients at positions wb .. wb + 512 nt - 1 from products of fp32
 // (16 x 16 blocks, steps of four positions, three real products a complex one).
-// A branch's taps, zeros on either side, follow g in the planes.
-constexpr int kGxTapAt = 512 * 2 + 80, kGxTapLen = PRUNE_MAX_L + 32;
+// g has a pad word per 16 in the planes (a step's lanes read 16 words apart);
+// a branch's taps, zeros on either side, follow it.
+constexpr int kGxTapAt = (512 * 2 + 80) / 16 * 17, kGxTapLen = PRUNE_MAX_L + 32;
 __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, uint32_t Lmax, int wb, int nt, GxOut o,
                                      float *plane, int pitch, int lane) {
   const int n = (int)F.n, li = lane & 15, lk = lane >> 4;
@@ -194,25 +196,34 @@ __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, 
   for (int k = lane; k < 512 * nt + 80; k += 64) {
     const int q = wb + k;
     const float2 v = q >= 0 && q < n ? ld_global(F.g + q) : make_float2(0.f, 0.f);
-    plane[k] = v.x;
-    plane[pitch + k] = v.y;
+    plane[k + (k >> 4)] = v.x;
+    plane[pitch + k + (k >> 4)] = v.y;
   }
   wave_lds_fence();
-  for (int t = 0; t < 2 * nt; ++t) {
+  for (int t = 0; t < 2 * nt; t += 2) {   // two blocks of 256 at a time
     const int m0 = wb + 256 * t + 16 * li + 4 * lk;
-    float xr[4], xi[4], rr[4], pr[4], pi[4], qr[4], qi[4];
+    float xr[2][4], xi[2][4], rr[2][4], pr[2][4], pi[2][4], qr[2][4], qi[2][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int m = m0 + e;
-      const float2 v = m < n && m >= -(int)F.t0 ? ld_global(F.x + m) : make_float2(0.f, 0.f);
-      xr[e] = v.x;
-      xi[e] = v.y;
-      rr[e] = sqrtf(v.x * v.x + v.y * v.y);
-      pr[e] = pi[e] = qr[e] = qi[e] = 0.f;
-    }
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + 256 * u + e;
+        const float2 v = m < n && m >= -(int)F.t0 ? ld_global(F.x + m) : make_float2(0.f, 0.f);
+        xr[u][e] = v.x;
+        xi[u][e] = v.y;
+        rr[u][e] = sqrtf(v.x * v.x + v.y * v.y);
+        pr[u][e] = pi[u][e] = qr[u][e] = qi[u][e] = 0.f;
+      }
     for (int p = (int)d.Kmax - 1; p >= 0; --p) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { pr[e] *= rr[e]; pi[e] *= rr[e]; qr[e] *= rr[e]; qi[e] *= rr[e]; }
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          pr[u][e] *= rr[u][e];
+          pi[u][e] *= rr[u][e];
+          qr[u][e] *= rr[u][e];
+          qi[u][e] *= rr[u][e];
+        }
       for (uint32_t bank = 0; bank < d.n_banks; ++bank) {
         if (!((F.mask >> (bank * d.Kmax)) & kfull & (1u << p))) continue;
         const int L = (int)d.L[bank];
@@ -224,32 +235,42 @@ __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, 
           plane[pitch + kGxTapAt + k] = h.y;
         }
         wave_lds_fence();
-        floatx4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0, a2 = a0;
+        floatx4 a0[2], a1[2], a2[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) a0[u] = a1[u] = a2[u] = floatx4{0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < (L + 15 + 3) / 4; ++s) {
           const int l = kGxTapAt + 16 + 4 * s + lk - li;
-          const float2 h = make_float2(plane[l], plane[pitch + l]);
-          const int w = 256 * t + 16 * li + 4 * s + lk;
-          const float gr = plane[w], gi = plane[pitch + w];
-          a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.x, gr, a0, 0, 0, 0);
-          a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(-h.y, gi, a1, 0, 0, 0);
-          a2 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.x - h.y, gr + gi, a2, 0, 0, 0);
+          const float hr = plane[l], hi = plane[pitch + l];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int k = 256 * (t + u) + 16 * li + 4 * s + lk, w = k + (k >> 4);
+            const float gr = plane[w], gi = plane[pitch + w];
+            a0[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(hr, gr, a0[u], 0, 0, 0);
+            a1[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(-hi, gi, a1[u], 0, 0, 0);
+            a2[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(hr - hi, gr + gi, a2[u], 0, 0, 0);
+          }
         }
         const float ph = 0.5f * (float)p;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float gr = a0[e] - a1[e], gi = a2[e] - a0[e] - a1[e];
-          pr[e] += gr;
-          pi[e] += gi;
-          qr[e] = fmaf(ph, gr, qr[e]);
-          qi[e] = fmaf(ph, gi, qi[e]);
-        }
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float gr = a0[u][e] - a1[u][e], gi = a2[u][e] - a0[u][e] - a1[u][e];
+            pr[u][e] += gr;
+            pi[u][e] += gi;
+            qr[u][e] = fmaf(ph, gr, qr[u][e]);
+            qi[u][e] = fmaf(ph, gi, qi[u][e]);
+          }
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int m = m0 + e;
-      if (m >= o.lo && m < o.hi) st_global(o.gx + m, gx_combine<false>(xr[e], xi[e], pr[e], pi[e], qr[e], qi[e]));
-    }
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + 256 * u + e;
+        if (m >= o.lo && m < o.hi)
+          st_global(o.gx + m, gx_combine<false>(xr[u][e], xi[u][e], pr[u][e], pi[u][e], qr[u][e], qi[u][e]));
+      }
   }
   wave_lds_fence();
 }
@@ -258,6 +279,45 @@ __device__ __noinline__ void gx_fp32(const prune_fb_desc &d, const BwdFrame &F, 
 template <int NT>
 __device__ __forceinline__ int output_at(int lane, int b) {
   return 16 * NT * (lane & 31) + 2 * (lane >> 5) + 16 * (b >> 3) + 4 * ((b >> 1) & 3) + (b & 1);
+}
+
+// The outputs in `few` (a bit for each of the lane's) by the definition in fp32,
+// one after another, a lane for each tap.
+template <int NT>
+__device__ __noinline__ void fix_outputs(const prune_fb_desc &d, const BwdFrame &F, uint32_t Lmax, int wb, GxOut o,
+                                         uint32_t few, int lane) {
+  const int n = (int)F.n;
+  for (;;) {
+    const unsigned long long who = __ballot(few != 0u);
+    if (!who) break;
+    const int src = __ffsll(who) - 1, b = __ffs(__builtin_amdgcn_readlane((int)few, src)) - 1;
+    const int m = wb + output_at<NT>(src, b), q = m + lane;
+    const float2 x = m >= -(int)F.t0 ? ld_global(F.x + m) : make_float2(0.f, 0.f);   // (m < n)
+    const float2 g = q >= 0 && q < n ? ld_global(F.g + q) : make_float2(0.f, 0.f);
+    const float r = sqrtf(x.x * x.x + x.y * x.y);
+    float pr = 0.f, pi = 0.f, qr = 0.f, qi = 0.f;
+    for (int p = (int)d.Kmax - 1; p >= 0; --p) {
+      float gr = 0.f, gi = 0.f;
+      for (uint32_t bank = 0; bank < d.n_banks; ++bank) {
+        const uint32_t br = bank * d.Kmax + p;
+        if (!((F.mask >> br) & 1u) || lane >= (int)d.L[bank]) continue;
+        const float2 h = ld_global(F.taps + (size_t)br * Lmax + lane);
+        gr += fmaf(h.x, g.x, h.y * g.y);
+        gi += fmaf(h.x, g.y, -h.y * g.x);
+      }
+      for (int k = 32; k; k >>= 1) {
+        gr += __shfl_xor(gr, k, 64);
+        gi += __shfl_xor(gi, k, 64);
+      }
+      const float ph = 0.5f * (float)p;
+      pr = fmaf(pr, r, gr);
+      pi = fmaf(pi, r, gi);
+      qr = fmaf(qr, r, ph * gr);
+      qi = fmaf(qi, r, ph * gi);
+    }
+    if (lane == 0) st_global(o.gx + m, gx_combine<false>(x.x, x.y, pr, pi, qr, qi));
+    if (lane == src) few &= few - 1u;
+  }
 }
 
 // Whether g is zero over the L samples from each output in `zeros` (a bit for
@@ -293,13 +353,15 @@ __device__ __noinline__ bool silent_after(const BwdFrame &F, int wb, int L, uint
 }
 
 // One pass of one wave: positions wb .. wb + 512 NT - 1 (32 columns of 16 NT).
-// kPassLeft: nothing is written, the outputs are left to gx_fp32.  kPassZeros:
-// everything is written, and right if g is zero after the outputs in `zeros`
-// (silent_after); else the outputs are left to gx_fp32.
-enum { kPassDone, kPassLeft, kPassZeros };
+// kPassLeft: nothing is written, the outputs are left to gx_fp32.  kPassCheck:
+// everything is written; the outputs in the upper half of `flags` (a bit for
+// each of the lane's) are to be evaluated again, and where g is not zero after
+// one in the lower half (silent_after), all are left to gx_fp32.
+enum { kPassDone, kPassLeft, kPassCheck };
+constexpr int kFew = 12;
 template <int NT, int S, int PLANE>
 __device__ __forceinline__ int gx_pass(const BwdFrame &F, int wb, uint32_t pm, GxOut o, const GxShared &sh,
-                                       uint32_t *__restrict__ plane, int lane, uint32_t &zeros) {
+                                       uint32_t *__restrict__ plane, int lane, uint32_t &flags) {
   constexpr int NP = 4 * NT + 1;               // sample pairs per lane
   constexpr int NC = 2 * NT + S - 2;           // chunk pairs per column
   constexpr int CW = 4 * NT;                   // chunks per column
@@ -475,7 +537,7 @@ __device__ __forceinline__ int gx_pass(const BwdFrame &F, int wb, uint32_t pm, G
   // the outputs against what may be missing of them: against T at the largest
   // r first, and each against its own where that does not settle it (at least
   // 2^-80, so that no power that is missing for its ef or by underflow counts)
-  zeros = 0;
+  flags = 0;
   if (A != 0 && eb > kNoTap / 2) {
     auto size = [&](int b) {
       const int j = b >> 3, q = 2 * (b & 7), m = wb + output_at<NT>(lane, b);
@@ -494,7 +556,8 @@ __device__ __forceinline__ int gx_pass(const BwdFrame &F, int wb, uint32_t pm, G
     for (int b = 0; b < 8 * NT; ++b)
       least = fminf(least, whole ? fmaxf(fabsf(P[b >> 3][2 * (b & 7)]), fabsf(P[b >> 3][2 * (b & 7) + 1])) : size(b));
     if (__any(least < 8.f * fmaxf(tm, 0x1p-80f))) {
-      bool low = false, quiet = true, some = false;
+      bool quiet = true, some = false;
+      int few = 0;
       for (int j = 0; j < NT; ++j) {
         float T[8];
 #pragma unroll
@@ -509,13 +572,14 @@ __device__ __forceinline__ int gx_pass(const BwdFrame &F, int wb, uint32_t pm, G
           const float r = NT > 1 && j ? rr[NT - 1][b] : rr[0][b];
           const float m = NT > 1 && j ? size(8 * (NT - 1) + b) : size(b);
           const float thr = r > 0.f || (pm & 1u) ? fmaxf(T[b], 0x1p-80f) : 0.f;
-          low |= m > 0.f && m < thr;
+          const bool low = m > 0.f && m < thr;
+          few += __popcll(__ballot(low));
           quiet &= m < 8.f * thr || m == kHuge;
           some |= m > 0.f && m < kHuge;
-          zeros |= m == 0.f && thr > 0.f ? 1u << (8 * j + b) : 0u;
+          flags |= low ? 0x10000u << (8 * j + b) : m == 0.f && thr > 0.f ? 1u << (8 * j + b) : 0u;
         }
       }
-      if (__any(low || (quiet && some))) return kPassLeft;
+      if (few > kFew || __any(quiet && some)) return kPassLeft;
     }
   }
 #pragma unroll
@@ -549,7 +613,7 @@ __device__ __forceinline__ int gx_pass(const BwdFrame &F, int wb, uint32_t pm, G
       else if (m + 1 >= o.lo && m + 1 < o.hi) st_global(o.gx + m + 1, make_float2(z.z, z.w));
     }
   }
-  return __any(zeros != 0u) ? kPassZeros : kPassDone;
+  return __any(flags != 0u) ? kPassCheck : kPassDone;
 }
 }  // namespace
 
@@ -634,22 +698,26 @@ __global__ __launch_bounds__(64 * kGxWaves, 2) void k_bwd_gx_split(prune_fb_desc
       if (!my) continue;
       const int nt = !halo && n - n0 > 512 ? 2 : 1;
       int end;
-      uint32_t zeros = 0;
+      uint32_t flags = 0;
       if (nt == 2) {
-        if (L <= 33) end = gx_pass<2, 6, PL>(F, n0, pm, o, sh, plane, lane, zeros);
-        else if (L <= 49) end = gx_pass<2, 8, PL>(F, n0, pm, o, sh, plane, lane, zeros);
-        else end = gx_pass<2, 10, PL>(F, n0, pm, o, sh, plane, lane, zeros);
+        if (L <= 33) end = gx_pass<2, 6, PL>(F, n0, pm, o, sh, plane, lane, flags);
+        else if (L <= 49) end = gx_pass<2, 8, PL>(F, n0, pm, o, sh, plane, lane, flags);
+        else end = gx_pass<2, 10, PL>(F, n0, pm, o, sh, plane, lane, flags);
       } else {
-        if (L <= 33) end = gx_pass<1, 6, PL>(F, n0, pm, o, sh, plane, lane, zeros);
-        else if (L <= 49) end = gx_pass<1, 8, PL>(F, n0, pm, o, sh, plane, lane, zeros);
-        else end = gx_pass<1, 10, PL>(F, n0, pm, o, sh, plane, lane, zeros);
+        if (L <= 33) end = gx_pass<1, 6, PL>(F, n0, pm, o, sh, plane, lane, flags);
+        else if (L <= 49) end = gx_pass<1, 8, PL>(F, n0, pm, o, sh, plane, lane, flags);
+        else end = gx_pass<1, 10, PL>(F, n0, pm, o, sh, plane, lane, flags);
       }
-      if (end == kPassZeros) {
-        const bool silent = nt == 2 ? silent_after<2>(sh.frame[par][k], n0, L, zeros, plane, lane)
-                                    : silent_after<1>(sh.frame[par][k], n0, L, zeros, plane, lane);
-        if (!silent) end = kPassLeft;
+      if (end == kPassCheck) {
         __builtin_amdgcn_s_waitcnt(0);         // for the outputs that are written again
         asm volatile("" ::: "memory");
+        const BwdFrame &f = sh.frame[par][k];
+        const uint32_t zeros = flags & 0xffffu;
+        if (__any(zeros != 0u) && !(nt == 2 ? silent_after<2>(f, n0, L, zeros, plane, lane)
+                                            : silent_after<1>(f, n0, L, zeros, plane, lane)))
+          end = kPassLeft;
+        else if (nt == 2) fix_outputs<2>(d, f, Lmax, n0, o, flags >> 16, lane);
+        else fix_outputs<1>(d, f, Lmax, n0, o, flags >> 16, lane);
       }
       if (end == kPassLeft) gx_fp32(d, sh.frame[par][k], Lmax, n0, nt, o, (float *)plane, PL, lane);
     }
