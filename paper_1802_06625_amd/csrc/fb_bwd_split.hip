@@ -13,18 +13,20 @@
 // sign changed, for the imaginary part.  The sum does not depend on the bank:
 // every bank whose mask holds the power takes its taps from the same result.
 //
-// Precision.  g and x of a chunk of 256 positions are scaled by powers of two
-// so that the largest component lies in [2^10, 2^11), and every g and u_p is
-// the sum of two half-precision parts (split_pair).  high x high is summed
-// apart from low x high + high x low, exactly but for one rounding per eight
-// terms; a chunk's sums are added up in fp32, and the tile partials in fp64
-// (bwd_common.h).  Relative error against fp64 for 4 to 64 taps and 2 to 10
-// powers: 1.5e-7 to 2.1e-7, where products of fp32 on the matrix cores had
-// 1.9e-7 to 3.1e-7.  The chunk is summed by the fp32 definition instead where
-// x or g is not finite or beyond 2^93, or where a run of eight samples of g
-// inside the frame (any sample below 15 taps) lies more than 2^11 below the
-// chunk's largest: otherwise the largest samples, which set the scale, count
-// in the sum.
+// Precision.  g and every power of x of a chunk of 256 positions are scaled by
+// powers of two so that the largest lies near 2^15, and are the sum of two
+// half-precision parts (split_pair).  high x high is summed apart from low x
+// high + high x low, exactly but for one rounding per eight terms; a chunk's
+// sums are added up in fp32, and the tile partials in fp64 (bwd_common.h).
+// Relative error against fp64 for 4 to 64 taps and 2 to 10 powers: 1.5e-7 to
+// 2.1e-7, where products of fp32 on the matrix cores had 1.9e-7 to 3.1e-7.
+// The parts can miss 2^-25 of a scaled value, so a sum of a chunk misses no
+// more than T = 2^-25 of the sum of g's magnitudes (and 2^16 for each component
+// of g below one half; its rms is a twentieth of that or less).  Where a run's
+// sum of any active power and tap lies below 2^17 of its chunks' T, the run is
+// summed by the fp32 definition instead; so is a chunk where x or g is not finite or beyond 2^93.  (The check
+// is on a run's sums, not a chunk's: beside a masked stretch of g a chunk has
+// sums of a few terms, whatever they are, at most filter lengths.)
 //
 // What bounds it.  1024 frames x 32768 of 64 streams, 30 % of them skipped, 64
 // taps, 7 powers: 300 us, from 745 us for v_mfma_f32_16x16x4_f32 over 16 x 16
@@ -42,7 +44,8 @@ namespace prune {
 namespace {
 constexpr int kGhWaves = 4;
 constexpr int kGhCh = 256;                  // input positions per chunk
-constexpr int kGhBits = 11;                 // components are scaled below 2^11
+constexpr int kGhBits = 15;                 // components are scaled below 2^15
+constexpr float kGhMargin = 0x1p-8f;        // 2^17 times an operand's 2^-25
 constexpr int kGhPow = 8;                   // powers per column group
 constexpr int kGhUP = kGhCh + 4;            // words of a basis plane: rows of eight powers hit distinct banks
 constexpr int kGhGP = kGhCh + PRUNE_MAX_L + 4;
@@ -52,7 +55,8 @@ struct GhWave {
   uint32_t g[2][kGhGP];
 };
 constexpr int kGhTot = 2 * PRUNE_MAX_L * 16;   // sums of a wave: [column group][tap][column]
-static_assert(sizeof(GhWave::u) >= kGhTot * sizeof(float), "the sums fit in the basis planes");
+constexpr int kGhErr = kGhTot;                 // and 2^17 T: [column group][column]
+static_assert(sizeof(GhWave::u) >= (kGhTot + 32) * sizeof(float), "the sums fit in the basis planes");
 
 // r^e for 0 <= e < 16 by binary powering, without branches.
 __device__ __forceinline__ float ipow(float r, int e) {
@@ -66,26 +70,31 @@ __device__ __forceinline__ float ipow(float r, int e) {
 }
 
 // Sums of a chunk by the fp32 definition, in the matrix-core layout:
-// out[((group * 4 + row tile) * 64 + lane) * 4 + e].  Input positions a ..
-// a + 255 in [-t0, pend), cotangent in [0, n).
-__device__ __noinline__ void gh_chunk_fp32(const float2 *x, const float2 *g, int t0, int pend, int n, int a, int KH,
-                                           int RT, float *out, int lane) {
+// out[((group * 4 + row tile) * 64 + lane) * 4 + e].  in: re, im and magnitude
+// of the chunk's samples, re and im of the cotangents (kGhCh and PRUNE_MAX_L
+// more), zeros outside the frame.
+constexpr int kGhIn = 3 * kGhCh + 2 * (kGhCh + PRUNE_MAX_L);
+static_assert(sizeof(GhWave::u) >= (kGhIn + kGhTot) * sizeof(float), "a chunk and its sums fit in the basis planes");
+template <int RT>
+__device__ __noinline__ void gh_chunk_fp32(const float *in, float *out, int KH, int lane) {
   const int li = lane & 15, dp = lane >> 5, comp = (lane >> 4) & 1;
+  const float *g = in + 3 * kGhCh + comp * (kGhCh + PRUNE_MAX_L);
   for (int grp = 0; 8 * grp < KH; ++grp) {
     const int power = 8 * grp + (li >> 1);
-    for (int rt = 0; rt < RT; ++rt) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int s = 0; s < kGhCh / 2; ++s) {
-        const int p = a + 2 * s + dp, q = p + 16 * rt + li;
-        const float2 gv = q >= 0 && q < n ? ld_global(g + q) : make_float2(0.f, 0.f);
-        const float2 xv = p >= -t0 && p < pend ? ld_global(x + p) : make_float2(0.f, 0.f);
-        const float w = ipow(sqrtf(xv.x * xv.x + xv.y * xv.y), power);
-        const float ur = xv.x * w, ui = xv.y * w;
-        const float b = power >= KH ? 0.f : (li & 1) ? (comp ? ur : -ui) : (comp ? ui : ur);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(comp ? gv.y : gv.x, b, acc, 0, 0, 0);
-      }
-      *(floatx4 *)(out + ((grp * 4 + rt) * 64 + lane) * 4) = acc;
+    floatx4 acc[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < kGhCh / 2; ++s) {
+      const int p = 2 * s + dp;
+      const float w = ipow(in[2 * kGhCh + p], power);
+      const float ur = in[p] * w, ui = in[kGhCh + p] * w;
+      const float b = power >= KH ? 0.f : (li & 1) ? (comp ? ur : -ui) : (comp ? ui : ur);
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[p + 16 * t + li], b, acc[t], 0, 0, 0);
     }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) *(floatx4 *)(out + ((grp * 4 + t) * 64 + lane) * 4) = acc[t];
   }
 }
 
@@ -136,9 +145,10 @@ __device__ __forceinline__ void gh_products(const uint32_t *gp, const uint32_t *
 }
 
 // A wave's chunks w, w + 4, ... of a run: input positions [a0, pend) of frame
-// F, RT row tiles of taps, KH powers.  The sums go to the wave's T.
+// F, RT row tiles of taps, KH powers, by the fp32 definition if `whole`.  The
+// sums go to the wave's T, and after them 2^17 times what they may miss.
 template <int RT>
-__device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int KH, bool single, GhWave &sh, int lane,
+__device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int KH, bool whole, GhWave &sh, int lane,
                                        int w) {
   asm volatile("" : "+v"(lane));
   const int n = (int)F.n, t0 = (int)F.t0;
@@ -151,6 +161,7 @@ __device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int 
   for (int k = 0; k < 2; ++k)
 #pragma unroll
     for (int t = 0; t < RT; ++t) tot[k][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float err[2] = {0.f, 0.f};
   // lane l: positions 4 l .. 4 l + 3 of x and g, and position 256 + l of g
   pair_u xv[2], gv[2];
   float2 ge = make_float2(0.f, 0.f);
@@ -180,37 +191,43 @@ __device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int 
   if (a < pend) load(a);
   for (; a < pend; a += kGhCh * kGhWaves) {
     // scales and guards
-    uint32_t xm = 0, gm[4], gmax = 0;
+    uint32_t xm = 0, gm = 0, gmin = ~0u;   // gmin: the least component of g that is not zero, less one
+    float gsum = 0.f;
+    auto take = [&](float v) {
+      gm = max(gm, abs_bits(v));
+      gmin = min(gmin, abs_bits(v) - 1u);
+      gsum += fabsf(v);
+    };
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       xm = max(xm, max(max(abs_bits(xv[q].x), abs_bits(xv[q].y)), max(abs_bits(xv[q].z), abs_bits(xv[q].w))));
-      gm[2 * q] = max(abs_bits(gv[q].x), abs_bits(gv[q].y));
-      gm[2 * q + 1] = max(abs_bits(gv[q].z), abs_bits(gv[q].w));
+      take(gv[q].x); take(gv[q].y); take(gv[q].z); take(gv[q].w);
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) gmax = max(gmax, gm[q]);
-    const uint32_t own = gmax;
-    gmax = max(gmax, max(abs_bits(ge.x), abs_bits(ge.y)));
-    const uint32_t X = (uint32_t)wave_max((int)xm), G = (uint32_t)wave_max((int)gmax);
-    const bool bad = (X != 0 && (X < kLow || X >= kHigh)) || (G != 0 && (G < kLow || G >= kHigh));
+    take(ge.x);
+    take(ge.y);
+    const uint32_t X = (uint32_t)wave_max((int)xm), G = (uint32_t)wave_max((int)gm);
+    const bool bad = whole || (X != 0 && (X < kLow || X >= kHigh)) || (G != 0 && (G < kLow || G >= kHigh));
     if (!bad && (X == 0 || G == 0)) {
       if (a + kGhCh * kGhWaves < pend) load(a + kGhCh * kGhWaves);
       continue;
     }
-    const uint32_t thr = G - ((uint32_t)kGhBits << 23);
-    const int p0 = a + 4 * lane;
-    bool quiet = false;
-    if (single) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) quiet |= p0 + q >= 0 && p0 + q < n && gm[q] < thr;
-    } else {
-      const uint32_t m8 = max(own, (uint32_t)__builtin_amdgcn_update_dpp((int)own, (int)own, 0xB1, 0xf, 0xf, false));
-      quiet = p0 + 3 >= 0 && p0 < n && m8 < thr;
-    }
-    if (bad || __any(quiet)) {
-      float *out = (float *)&sh.u[0][0][0];
+    if (bad) {
+      float *in = (float *)&sh.u[0][0][0], *out = in + kGhIn, *gp = in + 3 * kGhCh;
       wave_lds_fence();
-      gh_chunk_fp32(F.x, F.g, t0, pend, n, a, KH, RT, out, lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const pair_u xq = xv[q >> 1], gq = gv[q >> 1];
+        const float re = q & 1 ? xq.z : xq.x, im = q & 1 ? xq.w : xq.y;
+        in[4 * lane + q] = re;
+        in[kGhCh + 4 * lane + q] = im;
+        in[2 * kGhCh + 4 * lane + q] = sqrtf(re * re + im * im);
+        gp[4 * lane + q] = q & 1 ? gq.z : gq.x;
+        gp[kGhCh + PRUNE_MAX_L + 4 * lane + q] = q & 1 ? gq.w : gq.y;
+      }
+      gp[kGhCh + lane] = ge.x;
+      gp[kGhCh + PRUNE_MAX_L + kGhCh + lane] = ge.y;
+      wave_lds_fence();
+      gh_chunk_fp32<RT>(in, out, KH, lane);
       wave_lds_fence();
 #pragma unroll
       for (int k = 0; k < 2; ++k)
@@ -230,10 +247,14 @@ __device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int 
     const float flip = (a / (kGhCh * kGhWaves)) & 1 ? -1.f : 1.f;
     const float xs = __builtin_bit_cast(float, (uint32_t)(127 + kGhBits - ex) << 23) * flip;
     const float gs = __builtin_bit_cast(float, (uint32_t)(127 + kGhBits - eg) << 23);
+    // components below one half (scaled; ten to a lane), and 2^17 T
+    const uint32_t half = (uint32_t)max(126 + eg - kGhBits, 0) << 23;
+    const float miss = kGhMargin * fmaf(wave_sum(gsum), gs, 0xap16f * (float)__popcll(__ballot(gmin < half)));
     // |x| as rho + rlo: a power's error would otherwise be |x|'s rounding, p
     // times, in the few largest samples that make up the sums of high powers
     pair_u v[2];
     float rho[4], rlo[4];
+    uint32_t top = 0;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       v[q] = xv[q] * xs;
@@ -241,12 +262,19 @@ __device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int 
       for (int k = 0; k < 2; ++k) {
         const float re = k ? v[q].z : v[q].x, im = k ? v[q].w : v[q].y;
         const float h2 = re * re, s2 = fmaf(im, im, h2), es = fmaf(im, im, h2 - s2) + fmaf(re, re, -h2);
+        top = max(top, __builtin_bit_cast(uint32_t, s2));
         const float y = __builtin_amdgcn_rsqf(fmaxf(s2, 1e-30f)), r0 = s2 * y;
         const float c = (fmaf(-r0, r0, s2) + es) * (0.5f * y), r = r0 + c;
         rho[2 * q + k] = r * (1.f / (1 << kGhBits));
         rlo[2 * q + k] = (c - (r - r0)) * (1.f / (1 << kGhBits));
       }
     }
+    // Power p is scaled up by 2^kp, so that its largest sample, |v| rho^p, lies
+    // near 2^15 too (no component reaches half precision's 65504).
+    const float lv =
+        0.5f * __builtin_amdgcn_logf(fmaxf(__builtin_bit_cast(float, (uint32_t)wave_max((int)top)), 0x1p28f));
+    auto lift = [&](int p) { return p ? (int)floorf(15.9f - lv - (float)p * (lv - kGhBits)) : 0; };
+    const int kp = lift(lane & 15);
     wave_lds_fence();   // the last chunk's reads end here
     {
       uint32_t hi[4], lo[4];
@@ -272,18 +300,23 @@ __device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int 
         split_pair(v[1], neg1, hi + 2, lo + 2);
         *(uintx4 *)&sh.u[0][j][4 * lane] = uintx4{hi[0], hi[1], hi[2], hi[3]};
         *(uintx4 *)&sh.u[1][j][4 * lane] = uintx4{lo[0], lo[1], lo[2], lo[3]};
+        const int p = 8 * k + j;
+        const float sc = __builtin_bit_cast(
+            float, (uint32_t)(127 + __builtin_amdgcn_readlane(kp, p + 1) - __builtin_amdgcn_readlane(kp, p)) << 23);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          v[q].x = fmaf(v[q].x, rho[2 * q], v[q].x * rlo[2 * q]);
-          v[q].y = fmaf(v[q].y, rho[2 * q], v[q].y * rlo[2 * q]);
-          v[q].z = fmaf(v[q].z, rho[2 * q + 1], v[q].z * rlo[2 * q + 1]);
-          v[q].w = fmaf(v[q].w, rho[2 * q + 1], v[q].w * rlo[2 * q + 1]);
+          const float h0 = rho[2 * q] * sc, l0 = rlo[2 * q] * sc, h1 = rho[2 * q + 1] * sc, l1 = rlo[2 * q + 1] * sc;
+          v[q].x = fmaf(v[q].x, h0, v[q].x * l0);
+          v[q].y = fmaf(v[q].y, h0, v[q].y * l0);
+          v[q].z = fmaf(v[q].z, h1, v[q].z * l1);
+          v[q].w = fmaf(v[q].w, h1, v[q].w * l1);
         }
       }
       wave_lds_fence();
       floatx4 acc[RT];
       gh_products<RT>(gp, up, nq, rot, sgn, acc);
-      const int p = 8 * k + (li >> 1), sc = eg + ex - 2 * kGhBits + p * ex;
+      const int p = 8 * k + (li >> 1), sc = eg + ex - 2 * kGhBits + p * ex - lift(p);
+      err[k] += ldexpf(miss, sc);
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
@@ -299,6 +332,9 @@ __device__ __forceinline__ void gh_run(const BwdFrame &F, int a0, int pend, int 
     for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int e = 0; e < 4; ++e) T[(k * PRUNE_MAX_L + 16 * t + 4 * kg + e) * 16 + li] = tot[k][t][e];
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (lane < 16) T[kGhErr + 16 * k + li] = err[k];
 }
 }  // namespace
 
@@ -339,38 +375,45 @@ __global__ __launch_bounds__(64 * kGhWaves, 2) void k_bwd_gh_split(prune_fb_desc
       const uint32_t r1 = r0 + __ffs(other) - 1;
       const BwdFrame F = bf[w0.frame];
       float2 *row = partial + (size_t)r0 * E;
-      uint32_t pm = 0, L = 0, Ls = PRUNE_MAX_L;
+      uint32_t pm = 0, L = 0;
       for (uint32_t bank = 0; bank < d.n_banks; ++bank) {
         const uint32_t bm = F.route ? 0u : (F.mask >> (bank * d.Kmax)) & kfull;
         pm |= bm;
-        if (bm) { L = max(L, d.L[bank]); Ls = min(Ls, d.L[bank]); }
+        if (bm) L = max(L, d.L[bank]);
       }
-      if (pm) {
-        const int KH = 32 - __clz(pm), n = (int)F.n;
-        // input positions: this run's samples, and the history of the frame's first tile
-        const int a0 = w0.tile ? (int)w0.tile * kBT : (L > 1 ? -PRUNE_MAX_L : 0);
-        const int pend = min(n, ((int)w0.tile + (int)(r1 - r0)) * kBT);
-        const bool single = Ls < 15;
-        if (L <= 16) gh_run<1>(F, a0, pend, KH, single, s_w[w], lane, w);
-        else if (L <= 32) gh_run<2>(F, a0, pend, KH, single, s_w[w], lane, w);
-        else if (L <= 48) gh_run<3>(F, a0, pend, KH, single, s_w[w], lane, w);
-        else gh_run<4>(F, a0, pend, KH, single, s_w[w], lane, w);
-      }
-      __syncthreads();
-      for (uint32_t k = t; k < E; k += 64 * kGhWaves) {
-        const uint32_t br = k / Lmax, l = k - br * Lmax, bank = br / d.Kmax, p = br - bank * d.Kmax;
-        float2 v = make_float2(0.f, 0.f);
-        if (pm && ((F.mask >> br) & 1u) && l < d.L[bank]) {
-#pragma unroll
-          for (int q = 0; q < kGhWaves; ++q) {
-            const float *T = (const float *)&s_w[q].u[0][0][0] + ((p >> 3) * PRUNE_MAX_L + l) * 16 + 2 * (p & 7);
-            v.x += T[0];
-            v.y += T[1];
-          }
+      for (bool whole = false;;) {
+        if (pm) {
+          const int KH = 32 - __clz(pm), n = (int)F.n;
+          // input positions: this run's samples, and the history of the frame's first tile
+          const int a0 = w0.tile ? (int)w0.tile * kBT : (L > 1 ? -PRUNE_MAX_L : 0);
+          const int pend = min(n, ((int)w0.tile + (int)(r1 - r0)) * kBT);
+          if (L <= 16) gh_run<1>(F, a0, pend, KH, whole, s_w[w], lane, w);
+          else if (L <= 32) gh_run<2>(F, a0, pend, KH, whole, s_w[w], lane, w);
+          else if (L <= 48) gh_run<3>(F, a0, pend, KH, whole, s_w[w], lane, w);
+          else gh_run<4>(F, a0, pend, KH, whole, s_w[w], lane, w);
         }
-        row[k] = v;
+        __syncthreads();
+        bool low = false;
+        for (uint32_t k = t; k < E; k += 64 * kGhWaves) {
+          const uint32_t br = k / Lmax, l = k - br * Lmax, bank = br / d.Kmax, p = br - bank * d.Kmax;
+          float2 v = make_float2(0.f, 0.f);
+          if (pm && ((F.mask >> br) & 1u) && l < d.L[bank]) {
+            float miss = 0.f;
+#pragma unroll
+            for (int q = 0; q < kGhWaves; ++q) {
+              const float *T = (const float *)&s_w[q].u[0][0][0], *c = T + ((p >> 3) * PRUNE_MAX_L + l) * 16 + 2 * (p & 7);
+              v.x += c[0];
+              v.y += c[1];
+              miss += T[kGhErr + 16 * (p >> 3) + 2 * (p & 7)];
+            }
+            low |= fmaxf(fabsf(v.x), fabsf(v.y)) < miss;
+          }
+          row[k] = v;
+        }
+        // (also before the LDS is rewritten, by the run again or the next one)
+        if (!__syncthreads_or(low) || whole) break;
+        whole = true;
       }
-      __syncthreads();   // LDS is rewritten by the next run
       r0 = r1;
     }
   }

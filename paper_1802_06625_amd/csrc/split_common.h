@@ -50,11 +50,19 @@ __device__ __forceinline__ int wave_max(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
-// Largest value of each group of four lanes.
-__device__ __forceinline__ float quad_max(float v) {
-  const int b = __builtin_bit_cast(int, v);   // not negative: ordered as integers
-  const int c = max(b, __builtin_amdgcn_update_dpp(b, b, 0xB1, 0xf, 0xf, false));    // lanes 1 0 3 2
-  return __builtin_bit_cast(float, max(c, __builtin_amdgcn_update_dpp(c, c, 0x4E, 0xf, 0xf, false)));   // 2 3 0 1
+// Sum over a wave, in a fixed order.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);
+  v = dpp_add<0x143, 0xc>(v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __builtin_bit_cast(uint32_t, v) & 0x7fffffffu; }

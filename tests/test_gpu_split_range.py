@@ -207,3 +207,46 @@ def test_grad_x_samples_and_taps(what, mask):
         taps *= np.exp2(-2.0 * np.arange(L)).astype(np.float32)
         g[rng.uniform(size=n) < 0.1] *= np.float32(1e-9)
     _grad_x(x, g, taps, [(0, n, mask)], K, L, what)
+
+
+# ---- tap gradients: per entry |grad - ref| <= 2^-16 sum |g| |u|
+@pytest.mark.parametrize("L", [1, 10, 20, 64])
+@pytest.mark.parametrize("what", ["one in 700", "one in 64", "loud without cotangent", "quiet only", "masked", "faint ends", "comb"])
+def test_grad_taps(what, L):
+    announce(f"tap gradients {what}, L {L}")
+    rng = np.random.default_rng(L)
+    n, K = 9000, 10
+    x, g, k = _c(rng, n) * np.float32(0.3), _c(rng, n), np.arange(n)
+    if what == "one in 700":
+        g[k % 700 != 650] = 0
+    elif what == "one in 64":
+        g[k % 64 != 5] = 0
+    elif what == "loud without cotangent":
+        x[(k // 100) % 2 == 0] *= 64
+        g[(k // 100) % 2 == 0] = 0
+    elif what == "quiet only":
+        x[k % 2000 < 150] *= np.float32(2.0 ** -6)
+        g[k % 2000 >= 150 - L] = 0
+        g[k % 2000 < L] = 0
+    elif what == "masked":
+        g[(k // 1500) % 2 == 1] = 0
+    elif what == "comb":   # most taps see faint cotangents only
+        x[k % 8 != 0] = 0
+        g[k % 8 != 0] *= np.float32(1e-10)
+    else:
+        x[k % 512 > 500] *= np.float32(1e-6)
+        g[k % 512 < 400] *= np.float32(1e-9)
+    rows = [(0, 0, 3, 0x3FF, 0), (0, 3, 2900, 0x3FF, 0), (0, 2903, 1, 0x201, 0), (0, 2904, n - 2904, 0x3FE, 0)]
+    taps = _c(rng, 1, 1, K, L)
+    ops.set_bwd_variant(2)
+    try:
+        _, gt = ops.fb_backward(torch.from_numpy(x[None]).cuda(), torch.from_numpy(taps).cuda(), ops.frame_table(rows),
+                                torch.from_numpy(g[None]).cuda(), K, (L,), n, want_gx=False)
+        gt = gt[0].cpu().numpy()
+    finally:
+        ops.set_bwd_variant(0)
+    fr = [r[1:] for r in rows]
+    _, ref = fb_stream_adjoint(x, fr, taps[0], (L,), K, g)
+    _, size = fb_stream_adjoint(np.abs(x.astype(complex)), fr, taps[0], (L,), K, np.abs(g.astype(complex)))
+    off = np.abs(gt - ref)
+    assert np.all(off <= 2.0 ** -16 * np.real(size) + 1e-44), (what, L, np.max(off / np.maximum(np.real(size), 1e-40)))
