@@ -573,7 +573,8 @@ prune_status prune_fb_backward(const prune_fb_desc *desc, const void *x, const v
 /* Forward kernel variant: 0 = automatic (autotuned, cached), otherwise a
  * fixed variant index (see prune_fb_variant_name).  The split half-precision
  * kernels (mfma_split_*) take filter banks of at least 25 taps; on a shorter
- * one a fixed choice of them runs variant 1. */
+ * one a fixed choice of them runs variant 1 (prune_fb_forward_noalloc: or, for
+ * work that its list would not hold, the same arithmetic without a list). */
 prune_status prune_set_fb_variant(int variant);
 const char *prune_fb_variant_name(int variant);
 int prune_fb_variant_count(void);

@@ -327,17 +327,18 @@ prune_status prune_fb_forward_noalloc(const prune_fb_desc *desc, const void *x, 
     const size_t per = ((size_t)desc->max_frame_len + tile - 1) / tile;
     return (size_t)desc->n_frames * (per ? per : 1);
   };
-  // a set variant with larger tiles than its stand-in's still takes the work
-  // lists that only its own tiles fit
-  if (forced && count(variant) > PRUNE_NOALLOC_MAX_ITEMS) variant = forced;
+  // The limit is that of the set variant's tiles.  Work that fits those, but not
+  // its stand-in's smaller ones, needs no list in the one-launch form (the same
+  // vector arithmetic; at most 8 x 2^18 workgroups).
   const uint32_t tile = (uint32_t)fb_variant_tile(variant);
   const size_t items = count(variant);
-  if (desc->n_frames > PRUNE_NOALLOC_MAX_FRAMES || items > PRUNE_NOALLOC_MAX_ITEMS) {
+  const bool listless = forced && forced != variant && items > PRUNE_NOALLOC_MAX_ITEMS;
+  if (desc->n_frames > PRUNE_NOALLOC_MAX_FRAMES || (listless ? count(forced) : items) > PRUNE_NOALLOC_MAX_ITEMS) {
     set_last_error("prune_fb_forward_noalloc: more frames or tiles than its fixed workspace holds "
                    "(PRUNE_NOALLOC_MAX_FRAMES, PRUNE_NOALLOC_MAX_ITEMS)");
     return PRUNE_E_CAPACITY;
   }
-  if (!forced && fb_small_outputs(*desc)) {
+  if (listless || (!forced && fb_small_outputs(*desc))) {
     fb_small_launch(*desc, (const float2 *)x, (const float2 *)taps, (const prune_fb_frame *)frames, (float2 *)y,
                     (hipStream_t)stream, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? PRUNE_OK : PRUNE_E_HIP;

@@ -24,9 +24,10 @@
 // more than T = 2^-25 of the sum of g's magnitudes (and 2^16 for each component
 // of g below one half; its rms is a twentieth of that or less).  Where a run's
 // sum of any active power and tap lies below 2^17 of its chunks' T, the run is
-// summed by the fp32 definition instead; so is a chunk where x or g is not finite or beyond 2^93.  (The check
-// is on a run's sums, not a chunk's: beside a masked stretch of g a chunk has
-// sums of a few terms, whatever they are, at most filter lengths.)
+// summed by the fp32 definition instead; so is a chunk where x or g is not
+// finite or beyond 2^93.  (The check is on a run's sums, not a chunk's: beside a
+// masked stretch of g a chunk has sums of a few terms, whatever they are, at
+// most filter lengths.)
 //
 // What bounds it.  1024 frames x 32768 of 64 streams, 30 % of them skipped, 64
 // taps, 7 powers: 300 us, from 745 us for v_mfma_f32_16x16x4_f32 over 16 x 16
