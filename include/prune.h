@@ -415,7 +415,9 @@ prune_status prune_graph_stream_host(prune_graph_t g, prune_id src, prune_id cfg
  * f (equal to atr for an SRP, 1..atr for a PRUNE_PORT_PARAM port).
  * dev_samples: device pointer to the frames back to back (copied into the
  * FIFO when the source fires; must stay valid until then), or NULL when the
- * caller has already written frame f at prune_fifo_write_window(f).
+ * caller has already written frame f at prune_fifo_write_window(f), on the
+ * stream that fires it or on the null stream (a fire that follows a push comes
+ * after the null stream's work, on whatever stream).
  * Queued entries live in a ring of pinned host memory that the device reads
  * in place; a push that would overwrite entries the device may not have read
  * yet (fire calls return before the device runs them) waits for the

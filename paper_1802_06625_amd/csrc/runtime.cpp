@@ -204,7 +204,8 @@ struct prune_graph {
   BatchSet sets[2]{};
   uint32_t parity = 0;
   hipStream_t side_stream = nullptr;
-  hipEvent_t ev_emit[2]{}, ev_done[2]{}, ev_sync = nullptr;
+  hipEvent_t ev_emit[2]{}, ev_done[2]{}, ev_sync = nullptr, ev_null = nullptr;
+  bool pushed = false;      // pushes since the last fire
   bool done_valid[2]{};
   bool need_sync = true;    // the caller's stream has work the side stream must wait for
   // the newest fire was a pipelined batch: ev_emit of its set follows every
@@ -218,7 +219,7 @@ struct prune_graph {
 // Teardown reports nothing: errors here have no caller to go to.
 prune_graph::~prune_graph() {
   if (side_stream) (void)hipStreamSynchronize(side_stream);
-  for (hipEvent_t e : {ev_emit[0], ev_emit[1], ev_done[0], ev_done[1], ev_sync})
+  for (hipEvent_t e : {ev_emit[0], ev_emit[1], ev_done[0], ev_done[1], ev_sync, ev_null})
     if (e) (void)hipEventDestroy(e);
   if (side_stream) (void)hipStreamDestroy(side_stream);
   for (auto &kv : graphs) (void)hipGraphExecDestroy(kv.second);
@@ -1591,6 +1592,7 @@ prune_status prune_source_push(prune_graph_t g, prune_id src, const void *dev_sa
     off += host_counts[f];
   }
   A.q_tail += n;
+  g->pushed = true;
   if (dev_samples) A.q_ptrs += n;
   return PRUNE_OK;
 }
@@ -1614,6 +1616,7 @@ prune_status prune_config_push(prune_graph_t g, prune_id cfg, const prune_side_i
   prune_side_info *ring = (prune_side_info *)A.q_host;
   for (uint32_t f = 0; f < n; ++f) ring[A.slot(A.q_tail + f)] = side[f];
   A.q_tail += n;
+  g->pushed = true;
   return PRUNE_OK;
 }
 
@@ -1627,12 +1630,27 @@ prune_status prune_sink_bind_output(prune_graph_t g, prune_id snk, void *dev_out
   return sync_actor_dev(g, snk);
 }
 
+// A stream other than the null stream fires pushed frames after what the null
+// stream has in flight, where a program may write them (a push costs no wait
+// for that: one event a fire, none on the null stream).
+static prune_status after_null_stream(prune_graph *g, hipStream_t s) {
+  const bool wait = g->pushed && s;
+  g->pushed = false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (!wait || (hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)) return PRUNE_OK;
+  if (!g->ev_null) HIPCHECK(hipEventCreateWithFlags(&g->ev_null, hipEventDisableTiming));
+  HIPCHECK(hipEventRecord(g->ev_null, nullptr));
+  HIPCHECK(hipStreamWaitEvent(s, g->ev_null, 0));
+  return PRUNE_OK;
+}
+
 prune_status prune_graph_fire(prune_graph_t g, int mode, uint32_t max_firings, prune_stream_t stream,
                               uint64_t *fired) {
   TRY(check_graph(g, true));
   hipStream_t s = (hipStream_t)stream;
   for (uint32_t f = 0; f < g->fifos.size(); ++f)
     if (!g->fifos[f].storage) return fail(PRUNE_E_STATE, "fifo " + std::to_string(f) + " has no storage");
+  TRY(after_null_stream(g, s));
   uint64_t done = 0;
   if (mode == PRUNE_PER_FIRING) {
     // per-firing kernels update FIFO counters on the caller's stream: the
