@@ -10,7 +10,7 @@
 // which costs 2(KH-1)+4 fp32 FMAs per (n, l) instead of 4 KH (KH = highest
 // active branch + 1 of the bank; inactive lower branches get zero
 // coefficients).  The arithmetic is fp32 with FMA contraction; r is the
-// correctly rounded sqrtf(re^2 + im^2).
+// correctly rounded sqrtf of fmaf(re, re, im^2) (magnitude).
 //
 // Data layout: frames are complex64 (float2) blocks in HBM.  A work item is
 // one tile of T = J*WG consecutive outputs of one frame.  The tile's input
@@ -213,7 +213,7 @@ __device__ __forceinline__ void fb_tile(const TileIn &in, int n0, const BankL &b
         const int q = pidx<J>(k);
         sh.wre[q] = v[i].x;
         sh.wim[q] = v[i].y;
-        sh.wrr[q] = sqrtf(v[i].x * v[i].x + v[i].y * v[i].y);
+        sh.wrr[q] = magnitude(v[i].x, v[i].y);
       }
     }
 #pragma unroll

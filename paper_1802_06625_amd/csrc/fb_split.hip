@@ -271,7 +271,7 @@ __device__ __noinline__ void fp32_outputs(CDesc &d, int wb, float *plane, int la
       const int k = lane + 64 * i, a = k + k / J;
       plane[a] = z[i].x;
       plane[kF32Plane + a] = z[i].y;
-      plane[2 * kF32Plane + a] = sqrtf(z[i].x * z[i].x + z[i].y * z[i].y);
+      plane[2 * kF32Plane + a] = magnitude(z[i].x, z[i].y);
     }
     wave_lds_fence();
     float yr[J], yi[J];
@@ -326,7 +326,7 @@ __device__ __noinline__ void fix_outputs(CDesc &d, int wb, uint32_t few, int lan
     const int at = wb + output_at<NT>(src, b), p = at - lane;
     float2 z = make_float2(0.f, 0.f);
     if (p >= 0 || -p <= hv) z = ld_global((p >= 0 ? d.x : halo) + p);
-    const float r = sqrtf(z.x * z.x + z.y * z.y);
+    const float r = magnitude(z.x, z.y);
     float yr = 0.f, yi = 0.f;
     for (uint32_t bank = 0; bank < d.n_banks; ++bank) {
       const uint32_t bmask = (d.mask >> (bank * d.Kmax)) & kfull;

@@ -50,6 +50,10 @@ __device__ __forceinline__ int wave_max(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+// |re + i im| as every forward kernel rounds it (written out: the compiler may
+// fuse either square of re * re + im * im).
+__device__ __forceinline__ float magnitude(float re, float im) { return sqrtf(fmaf(re, re, im * im)); }
+
 // Sum over a wave, in a fixed order.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float dpp_add(float v) {
