@@ -275,7 +275,8 @@ def main():
                                   f"from control tokens, L={Lt} taps, one batched firing per step",
                       "frames": F, "frame_len": n, "taps": Lt, "Kmax": wl.Kmax,
                       "samples_per_step": samples, "mode": mode_name,
-                      "fb_variant": ops.variant_names()[g_variant - 1] if g_variant else None},
+                      "fb_variant": ops.variant_names()[g_variant - 1] if g_variant else None,
+                      "fb_operands": fb_operands(g_variant)},
            "event_ms_per_step": round(ev_ms_step, 4),
            "batched_graph_msamples": round(samples / (graph_ms * 1e-3) / 1e6, 1),
            "batched_stream_msamples": round(samples / (stream_ms * 1e-3) / 1e6, 1),
@@ -572,10 +573,14 @@ def bench_direct(name, steps, warmup):
     by_variant = {}
     if name in ("C4", "C5"):
         # every forward kernel forced in turn (vector Horner and split
-        # half-precision matrix-core), same launch configuration as the autotuned call
+        # half-precision matrix-core), same launch configuration as the autotuned
+        # call; a variant that another one stands in for (the split kernels
+        # below 25 taps) is left out
         for v, vname in enumerate(ops.variant_names(), start=1):
             ops.set_variant(v)
             try:
+                if ops.tuned_variant(x, fr, wl.Kmax, wl.bank_L, mfl) != v:
+                    continue
                 by_variant[vname] = round(_time_events(fwd, steps, warmup), 4)
             finally:
                 ops.set_variant(0)
@@ -888,6 +893,14 @@ def bench_motion(steps, warmup, batch=64):
     del g, mg
     torch.cuda.empty_cache()
     return res
+
+
+def fb_operands(variant):
+    """How the filter-bank forward's products take their float32 operands."""
+    from paper_1802_06625_amd import ops
+    if variant and ops.variant_names()[variant - 1].startswith("mfma_split"):
+        return "float32 as the sum of two half-precision parts, float32 sums"
+    return "float32"
 
 
 def bench_c3(steps, warmup):
