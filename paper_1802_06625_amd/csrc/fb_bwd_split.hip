@@ -30,12 +30,14 @@
 // most filter lengths.)
 //
 // What bounds it.  1024 frames x 32768 of 64 streams, 30 % of them skipped, 64
-// taps, 7 powers: 300 us, from 745 us for v_mfma_f32_16x16x4_f32 over 16 x 16
+// taps, 7 powers: 320 us, from 745 us for v_mfma_f32_16x16x4_f32 over 16 x 16
 // blocks of (phase, position) whose diagonals were added.  The samples alone
 // take 80 us at the copy rate, the matrix core 160 us, the vector unit about
 // as much (powers and their splits 40, rotations 30); two waves a SIMD overlap
 // them in part.  301 frames of 255 to 20011 samples, banks of 8, 16 and 32
-// taps, 10 powers: 30 us, from 98 us (each bank was summed by itself).
+// taps, 10 powers: 36 us, from 98 us (each bank was summed by itself); the check
+// of the sums takes 4 of them, 10 of the 320.  A run that is summed again takes
+// 20 us and more, in which its workgroup does nothing else.
 #include "bwd_common.h"
 #include "runtime_kernels.h"
 #include "split_common.h"
@@ -382,11 +384,13 @@ __global__ __launch_bounds__(64 * kGhWaves, 2) void k_bwd_gh_split(prune_fb_desc
         pm |= bm;
         if (bm) L = max(L, d.L[bank]);
       }
+      // input positions: this run's samples, and the history of the frame's first tile
+      const int n = (int)F.n, a0 = w0.tile ? (int)w0.tile * kBT : (L > 1 ? -PRUNE_MAX_L : 0);
+      // taps that reach beyond the frame from all of them have no term
+      const int reach = n - max(a0, -(int)F.t0);
       for (bool whole = false;;) {
         if (pm) {
-          const int KH = 32 - __clz(pm), n = (int)F.n;
-          // input positions: this run's samples, and the history of the frame's first tile
-          const int a0 = w0.tile ? (int)w0.tile * kBT : (L > 1 ? -PRUNE_MAX_L : 0);
+          const int KH = 32 - __clz(pm);
           const int pend = min(n, ((int)w0.tile + (int)(r1 - r0)) * kBT);
           if (L <= 16) gh_run<1>(F, a0, pend, KH, whole, s_w[w], lane, w);
           else if (L <= 32) gh_run<2>(F, a0, pend, KH, whole, s_w[w], lane, w);
@@ -407,7 +411,7 @@ __global__ __launch_bounds__(64 * kGhWaves, 2) void k_bwd_gh_split(prune_fb_desc
               v.y += c[1];
               miss += T[kGhErr + 16 * (p >> 3) + 2 * (p & 7)];
             }
-            low |= fmaxf(fabsf(v.x), fabsf(v.y)) < miss;
+            low |= (int)l < reach && fmaxf(fabsf(v.x), fabsf(v.y)) < miss;
           }
           row[k] = v;
         }
