@@ -351,7 +351,7 @@ __global__ __launch_bounds__(64 * kGhWaves, 2) void k_bwd_gh_split(prune_fb_desc
                                                                    unsigned int *__restrict__ ticket,
                                                                    float2 *__restrict__ partial) {
   __shared__ GhWave s_w[kGhWaves];
-  __shared__ uint32_t s_grp;
+  __shared__ uint32_t s_grp, s_low[2];   // s_low: a sum of this attempt, of the next, is too small
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   uint32_t Lmax = 1;
   for (uint32_t b = 0; b < d.n_banks; ++b) Lmax = max(Lmax, d.L[b]);
@@ -359,6 +359,8 @@ __global__ __launch_bounds__(64 * kGhWaves, 2) void k_bwd_gh_split(prune_fb_desc
   const uint32_t ni = *n_items;
   const uint32_t run = bwd_run_len(ni, gridDim.x), ng = (ni + run - 1) / run;
   const uint32_t kfull = (1u << d.Kmax) - 1u;
+  uint32_t par = 0;
+  if (t < 2) s_low[t] = 0;
   bool first = true;   // first run group by workgroup index, later ones by ticket
   for (;;) {
     if (t == 0) s_grp = first ? blockIdx.x : gridDim.x >= ng ? ng : gridDim.x + atomicAdd(ticket, 1u);
@@ -415,9 +417,12 @@ __global__ __launch_bounds__(64 * kGhWaves, 2) void k_bwd_gh_split(prune_fb_desc
           }
           row[k] = v;
         }
-        // (also before the LDS is rewritten, by the run again or the next one)
-        if (!__syncthreads_or(low) || whole) break;
-        whole = true;
+        if (low) s_low[par] = 1u;
+        if (t == 0) s_low[par ^ 1u] = 0u;
+        __syncthreads();   // the LDS is rewritten, by the run again or the next one
+        whole = !whole && __builtin_amdgcn_readfirstlane((int)s_low[par]);
+        par ^= 1u;
+        if (!whole) break;
       }
       r0 = r1;
     }
