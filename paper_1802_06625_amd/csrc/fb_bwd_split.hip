@@ -35,8 +35,8 @@
 // take 80 us at the copy rate, the matrix core 160 us, the vector unit about
 // as much (powers and their splits 40, rotations 30); two waves a SIMD overlap
 // them in part.  301 frames of 255 to 20011 samples, banks of 8, 16 and 32
-// taps, 10 powers: 36 us, from 98 us (each bank was summed by itself); the check
-// of the sums takes 4 of them, 10 of the 320.  A run that is summed again takes
+// taps, 10 powers: 34 us, from 98 us (each bank was summed by itself); the check
+// of the sums takes 3 of them, 10 of the 320.  A run that is summed again takes
 // 20 us and more, in which its workgroup does nothing else.
 #include "bwd_common.h"
 #include "runtime_kernels.h"
