@@ -540,10 +540,12 @@ static BwdLayout bwd_layout(const prune_fb_desc &d) {
 }
 
 // Whether the matrix-core form takes grad_x from split half-precision
-// operands: from 15 taps on, where every output's window holds a whole run of
-// eight samples, so that the kernel's range check covers each output.  At 16
-// taps and 8 powers it takes 42 us against 56 us for the products of fp32, at
-// 64 taps and 7 powers 430 us against 790.
+// operands: from 15 taps on, where it is the more exact (fp64 error 0.97e-7
+// against 1.14e-7 for the products of fp32 at 15 taps and one power, 1.19e-7
+// against 1.43e-7 at 8; below, one power's is the larger at many tap counts,
+// 8.1e-8 against 4.3e-8 at one tap, 1.03e-7 against 0.94e-7 at ten).  At 16 taps
+// and 8 powers (2M samples) it takes 42 us against 56 us, at 64 taps and 7
+// powers (33.5M, 30 % copied) 394 against 790.
 static bool bwd_split_gx(const prune_fb_desc &d) {
   return *std::min_element(d.L, d.L + d.n_banks) >= kSplitGxMinTaps;
 }

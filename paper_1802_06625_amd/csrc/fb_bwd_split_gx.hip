@@ -31,14 +31,14 @@
 // stay.  Gaussian samples have their |P|'s median near 2^33 T.
 //
 // What bounds it.  1024 frames x 32768 of 64 streams, 30 % of them skipped, 64
-// taps, 7 powers: 430 us, from 790 us for products of fp32 on the matrix core
+// taps, 7 powers: 394 us, from 790 us for products of fp32 on the matrix core
 // (k_bwd_gu_mfma); 256 frames x 8192, 16 taps, 8 powers: 42 us from 56.  The
 // matrix core takes 155 us of the former, the LDS 160 us, the vector unit 100
 // us, the samples 170 us at the copy rate, and a pass's loads and sums lie
-// before and after its products: two waves a SIMD overlap them in part.  One
-// power alone takes 280 us.  Lanes reading x and writing gradients in the
-// products' layout, two samples from each of 32 columns: 15 us more.  Groups
-// of 8 or 16 tiles a ticket: 432 and 474 us (uneven ends).
+// before and after its products: two waves a SIMD overlap them in part.  Lanes
+// reading x and writing gradients in the products' layout, two samples from
+// each of 32 columns: 15 us more.  Groups of 8 or 16 tiles a ticket: 6 and 48
+// us more (uneven ends).
 #include "bwd_common.h"
 #include "runtime_kernels.h"
 #include "split_common.h"
