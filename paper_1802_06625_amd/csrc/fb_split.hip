@@ -245,65 +245,61 @@ __device__ __forceinline__ void fp32_taps(const float *plane, int lane, int L, c
   }
 }
 
-// The wave's outputs by the fp32 definition (the vector kernels' Horner form,
-// eight outputs a lane, 512 outputs at a time), for waves that the scaled split
-// cannot take.  1024 x 16384, ten branches, 32 taps, every wave here after its
-// passes: 677 us (221 without; the vector kernel 292).  Not inlined: its
-// registers would cost the passes theirs (spills, 517 -> 600 us on the 4096 x
-// 16384 batch).
-template <int NT>
+// 512 of a wave's outputs by the fp32 definition (the vector kernels' Horner
+// form, eight outputs a lane), for waves that the scaled split cannot take.
+// 1024 x 16384, ten branches, 32 taps, every wave here after its passes: 677 us
+// (221 without; the vector kernel 292).  Not inlined: its registers would cost
+// the passes theirs (spills, 517 -> 600 us on the 4096 x 16384 batch).
 __device__ __noinline__ void fp32_outputs(CDesc &d, int wb, float *plane, int lane) {
   constexpr int J = kF32J;
   const float2 *halo = d.halo + ((int)d.Lmax - 1);
   const int n = (int)d.n, hv = (int)d.halo_valid;
   const uint32_t kfull = (1u << d.Kmax) - 1u;
-  for (int o0 = 0; o0 < 512 * NT && wb + o0 < n; o0 += 512) {
-    float2 z[kF32Win / 64];
+  float2 z[kF32Win / 64];
 #pragma unroll
-    for (int i = 0; i < kF32Win / 64; ++i) {
-      const int p = wb + o0 - kHist + lane + 64 * i;
-      z[i] = make_float2(0.f, 0.f);
-      if (p >= 0 ? p < n : -p <= hv) z[i] = ld_global((p >= 0 ? d.x : halo) + p);
-    }
-    wave_lds_fence();
-#pragma unroll
-    for (int i = 0; i < kF32Win / 64; ++i) {
-      const int k = lane + 64 * i, a = k + k / J;
-      plane[a] = z[i].x;
-      plane[kF32Plane + a] = z[i].y;
-      plane[2 * kF32Plane + a] = magnitude(z[i].x, z[i].y);
-    }
-    wave_lds_fence();
-    float yr[J], yi[J];
-#pragma unroll
-    for (int j = 0; j < J; ++j) yr[j] = yi[j] = 0.f;
-    for (uint32_t bank = 0; bank < d.n_banks; ++bank) {
-      const uint32_t bmask = (d.mask >> (bank * d.Kmax)) & kfull;
-      if (!bmask) continue;
-      const int KH = 32 - __clz(bmask), L = (int)d.L[bank];
-      const float2 *tb = d.taps + (size_t)bank * d.Kmax * d.Lmax;
-      float2 tap[kSplitPow];
-#pragma unroll
-      for (int b = 0; b < kSplitPow; ++b) {
-        tap[b] = make_float2(0.f, 0.f);
-        if (((bmask >> b) & 1u) && lane < L) tap[b] = ld_global(tb + (size_t)b * d.Lmax + lane);
-      }
-      switch (KH) {
-#define PRUNE_FP(k) case k: fp32_taps<k>(plane, lane, L, tap, yr, yi); break
-        PRUNE_FP(1); PRUNE_FP(2); PRUNE_FP(3); PRUNE_FP(4); PRUNE_FP(5);
-        PRUNE_FP(6); PRUNE_FP(7); PRUNE_FP(8); PRUNE_FP(9);
-        default: fp32_taps<10>(plane, lane, L, tap, yr, yi);
-#undef PRUNE_FP
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int p = wb + o0 + J * lane + j;
-      if (p < n)
-        for (uint32_t o = 0; o < d.n_y; ++o) st_global(d.y[o] + p, make_float2(yr[j], yi[j]));
-    }
-    wave_lds_fence();
+  for (int i = 0; i < kF32Win / 64; ++i) {
+    const int p = wb - kHist + lane + 64 * i;
+    z[i] = make_float2(0.f, 0.f);
+    if (p >= 0 ? p < n : -p <= hv) z[i] = ld_global((p >= 0 ? d.x : halo) + p);
   }
+  wave_lds_fence();
+#pragma unroll
+  for (int i = 0; i < kF32Win / 64; ++i) {
+    const int k = lane + 64 * i, a = k + k / J;
+    plane[a] = z[i].x;
+    plane[kF32Plane + a] = z[i].y;
+    plane[2 * kF32Plane + a] = magnitude(z[i].x, z[i].y);
+  }
+  wave_lds_fence();
+  float yr[J], yi[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) yr[j] = yi[j] = 0.f;
+  for (uint32_t bank = 0; bank < d.n_banks; ++bank) {
+    const uint32_t bmask = (d.mask >> (bank * d.Kmax)) & kfull;
+    if (!bmask) continue;
+    const int KH = 32 - __clz(bmask), L = (int)d.L[bank];
+    const float2 *tb = d.taps + (size_t)bank * d.Kmax * d.Lmax;
+    float2 tap[kSplitPow];
+#pragma unroll
+    for (int b = 0; b < kSplitPow; ++b) {
+      tap[b] = make_float2(0.f, 0.f);
+      if (((bmask >> b) & 1u) && lane < L) tap[b] = ld_global(tb + (size_t)b * d.Lmax + lane);
+    }
+    switch (KH) {
+#define PRUNE_FP(k) case k: fp32_taps<k>(plane, lane, L, tap, yr, yi); break
+      PRUNE_FP(1); PRUNE_FP(2); PRUNE_FP(3); PRUNE_FP(4); PRUNE_FP(5);
+      PRUNE_FP(6); PRUNE_FP(7); PRUNE_FP(8); PRUNE_FP(9);
+      default: fp32_taps<10>(plane, lane, L, tap, yr, yi);
+#undef PRUNE_FP
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int p = wb + J * lane + j;
+    if (p < n)
+      for (uint32_t o = 0; o < d.n_y; ++o) st_global(d.y[o] + p, make_float2(yr[j], yi[j]));
+  }
+  wave_lds_fence();
 }
 
 // A lane's output b of a wave (in the order of split_pass): its place from wb.
@@ -709,8 +705,8 @@ __global__ __launch_bounds__(256, 2) void k_fb_split(const FbFrameDesc *__restri
             else fix_outputs<1>(d, wb, flags >> 16, lane);
           }
           if (end == kPassLeft) {
-            if (two) fp32_outputs<NTMAX>(d, wb, (float *)plane, lane);
-            else fp32_outputs<1>(d, wb, (float *)plane, lane);
+            for (int o = 0; o < 512 * nt && wb + o < (int)d.n; o += 512)
+              fp32_outputs(d, wb + o, (float *)plane, lane);
           }
           prefetch();                          // (again: the calls took its registers)
         }
