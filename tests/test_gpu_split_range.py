@@ -3,8 +3,10 @@ the largest of its wave's window: quiet stretches beside loud ones with the
 high powers in front, masks and taps without the first power, taps that leave
 the loud samples out, single samples in silence, stream starts and frame ends.
 
-Forward, per output: |y - ref| <= 2^-17 sum |h| |u|, the kernels' own bound
-(110 roundings of 2^-24), and 1e-44 for fp32's underflow."""
+Forward, per output: |y - ref| <= 2^-17 sum |h| |u| and 1e-44 for fp32's
+underflow.  110 roundings of 2^-24 make 2^-17.2 at worst, and an output that is
+not evaluated again in fp32 may miss 2^-17 of itself at worst; both add up like
+squares, to a tenth of the bound."""
 import numpy as np
 import pytest
 import torch
